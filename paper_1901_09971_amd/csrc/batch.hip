@@ -50,6 +50,8 @@ struct dgf_batch {
     int64_t *d_item_off = nullptr, *d_pt_off = nullptr;
     uint32_t *d_counter = nullptr;
     AdjPair *d_adj = nullptr; // per-pair frames and gradient-map offsets for the adjoint
+    int64_t adj_tiles = 0;     // workgroups of the tiled adjoint, and the largest LDS tiles of a pair
+    size_t adj_tile_floats = 0;
     std::vector<int64_t> grad_off; // first float of each pair's dI0 (dI1 follows), P + 1 entries
     PyrJob *d_pyr = nullptr; // [(L-1)][2P]
     double *d_gm = nullptr;  // global-motion fit state (models, then partial sums), DGF_TRACK_GLOBAL only
@@ -337,8 +339,13 @@ int dgf_batch_create(const dgf_pair_desc *pairs, int32_t npairs, int32_t levels,
         const int64_t wh = (int64_t)d.I0.width * d.I0.height;
         const int64_t g0 = b->grad_off[i];
         adj[i] = AdjPair{(const uint8_t *)d.I0.data, (const uint8_t *)d.I1.data, d.I0.pitch_bytes, d.I1.pitch_bytes,
-                         g0, g0 + wh, d.I0.width, d.I0.width, d.I0.width, d.I0.height};
+                         g0, g0 + wh, d.I0.width, d.I0.width, d.I0.width, d.I0.height, 0, 0, 0, 0, 0, 0, 0, 0, 0};
         b->grad_off[i + 1] = g0 + 2 * wh;
+        if (!adjoint_support_compiled(support)) continue;
+        adjoint_tile_shape(adj[i], det[i].nx, det[i].ny, support, d.window, d.stride);
+        adj[i].tile_first = b->adj_tiles;
+        b->adj_tiles += adjoint_tiles(adj[i]);
+        b->adj_tile_floats = std::max(b->adj_tile_floats, adjoint_tile_floats(adj[i]));
     }
     b->h_lv = lv;
     bool ok = hipMemcpy(b->d_lv, lv.data(), sizeof(LevelPair) * lv.size(), hipMemcpyHostToDevice) == hipSuccess;
@@ -481,7 +488,9 @@ int dgf_batch_backward(dgf_batch *b, const float *points, const float *flow, con
     A.illum = im ? illum : nullptr;
     A.n = b->total_pts;
     fill_adjoint_constants(A, b->opts);
-    return launch_track_adjoint(A, b->dtype, st) == hipSuccess ? DGF_OK : DGF_ERR_HIP;
+    const hipError_t e = adjoint_support_compiled(b->s) ? launch_adjoint_tiled(A, b->adj_tiles, b->adj_tile_floats, st)
+                                                        : launch_track_adjoint(A, b->dtype, st);
+    return e == hipSuccess ? DGF_OK : DGF_ERR_HIP;
 }
 
 int dgf_batch_destroy(dgf_batch *b)

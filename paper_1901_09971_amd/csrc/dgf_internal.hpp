@@ -378,6 +378,19 @@ __device__ __forceinline__ bool stage_u8_w64(float *lds, int lp, const uint8_t *
     return true;
 }
 
+// A square rectangle (rows = cols) of at most 8 NS rows into LDS (B steps' loads in flight;
+// CROWS: its row count when fixed at compile time): the unrolled whole-wavefront form for uint8
+// images where it qualifies, stage_rect otherwise, its lane layout worked out there and then
+// (border tiles are rare, and the layout would otherwise hold registers for the whole launch).
+template <int LPP, typename PixT, int NS, int B, int CROWS = 0>
+__device__ __forceinline__ void stage_tile(float *lds, int lp, const uint8_t *base, int64_t pitch, int W, int H, int ox,
+                                           int oy, int rows, int cols, int li)
+{
+    if constexpr (LPP == 64 && sizeof(PixT) == 1)
+        if (stage_u8_w64<NS, B, CROWS>(lds, lp, base, pitch, W, H, ox, oy, rows, cols, li)) return;
+    stage_rect<LPP, PixT>(lds, lp, base, pitch, W, H, ox, oy, rows, cols, stage_lanes<LPP>(cols, li));
+}
+
 // i / d for 0 <= i < 2^16 and 1 <= d < 2^8, with inv = 1 / d: (i + 1/2) / d is at least 1 / (2 d)
 // away from the next integer and the float product errs by far less, so the truncation is exact.
 __device__ __forceinline__ int div_small(int i, float inv) { return (int)(((float)i + 0.5f) * inv); }
@@ -729,6 +742,11 @@ struct AdjPair {
     int64_t g0, g1;         // float offsets of the two gradient maps
     int64_t gpitch0, gpitch1;
     int32_t W, H;
+    // batch plans at a support fixed at compile time: the pair's points form a grid of nx x ny, taken
+    // in tiles of tx x ty by one workgroup each, with LDS tiles of w0 x h0 dI0 and w1 x h1 dI1 cells
+    // (none where they are zero); tile_first is the first workgroup of the pair
+    int64_t tile_first;
+    int32_t nx, ny, tx, ty, w0, h0, w1, h1;
 };
 
 struct AdjParams {
@@ -761,6 +779,12 @@ struct DetectGradParams {
 hipError_t launch_detect_backward(const DetectGradParams &G, hipStream_t st);
 
 hipError_t launch_track_adjoint(const AdjParams &A, int dtype, hipStream_t st);
+bool adjoint_support_compiled(int s); // a fixed-size adjoint exists for this support
+hipError_t launch_adjoint_direct(const AdjParams &A, hipStream_t st);
+void adjoint_tile_shape(AdjPair &P, int nx, int ny, int s, int win, int stride);
+size_t adjoint_tile_floats(const AdjPair &P);
+int64_t adjoint_tiles(const AdjPair &P);
+hipError_t launch_adjoint_tiled(const AdjParams &A, int64_t tiles, size_t tile_floats, hipStream_t st);
 void fill_adjoint_constants(AdjParams &A, const dgf_track_opts &o);
 
 // Tracker flags the library implements, and those that need the row-run kernel.

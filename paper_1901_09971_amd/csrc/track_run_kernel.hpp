@@ -94,19 +94,6 @@ __device__ __forceinline__ int uniform_floor_int(float f)
     return b < 0 ? -mag : mag;
 }
 
-// A square rectangle (rows = cols) of at most 8 NS rows into LDS (B steps' loads in flight;
-// CROWS: its row count when fixed at compile time): the unrolled whole-wavefront form for uint8
-// images where it qualifies, stage_rect otherwise, its lane layout worked out there and then
-// (border tiles are rare, and the layout would otherwise hold registers for the whole launch).
-template <int LPP, typename PixT, int NS, int B, int CROWS = 0>
-__device__ __forceinline__ void stage_tile(float *lds, int lp, const uint8_t *base, int64_t pitch, int W, int H, int ox,
-                                           int oy, int rows, int cols, int li)
-{
-    if constexpr (LPP == 64 && sizeof(PixT) == 1)
-        if (stage_u8_w64<NS, B, CROWS>(lds, lp, base, pitch, W, H, ox, oy, rows, cols, li)) return;
-    stage_rect<LPP, PixT>(lds, lp, base, pitch, W, H, ox, oy, rows, cols, stage_lanes<LPP>(cols, li));
-}
-
 // True when the flag is set on any lane of the wavefront.  With one point per wavefront (64 lanes
 // per point) every lane holds the same value, so the flag itself decides the branch: no ballot,
 // whose lowering would spend two vector instructions turning a mask back into a condition.
