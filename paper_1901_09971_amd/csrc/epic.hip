@@ -50,6 +50,7 @@ constexpr int kDefaultAsyncRelax = 32; // dgf_epic_async's relaxation launches w
 constexpr uint64_t kNoKey = ~0ull;
 constexpr uint64_t kDistCap = 0xFFFFFFFEull;
 constexpr int kMaxEdge = 510;        // largest edge-map value
+constexpr uint32_t kLeastCap = 1u << 30; // a least edge at or above this bounds nothing (distances stay below)
 
 enum : uint32_t { kErrDegree = 1u, kErrCand = 2u };
 
@@ -57,8 +58,8 @@ struct EpicWs {
     uint64_t *keys;  // [H*W]
     uint16_t *E;     // [H*W]
     uint64_t *adj;   // [n][kMaxDeg]: (edge length << 32) | neighbour, kNoKey = empty slot
-    float *model;    // [n][8]: affine coefficients (6), seed position (2)
-    uint32_t *ctr;   // [kChunk] tiles changed per relaxation launch, [1] error bits, [1] least edge,
+    float *model;    // [n][8]: affine coefficients (6), least edge of the seed (uint32 bits), unused
+    uint32_t *ctr;   // [kChunk] tiles changed per relaxation launch, [1] error bits, [1] unused,
                      // [kChunk] busy count per relaxation launch, [1] the changed count of the
                      // launch before the current group of kChunk
     uint32_t *mail;  // [kChunk][tiles]: a neighbour published keys into this tile's halo
@@ -94,7 +95,11 @@ __device__ __forceinline__ uint64_t load_key(const uint64_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Edge map and cleared key / adjacency tables / counters.
+// The least edge length of a seed's row.
+__device__ __forceinline__ uint32_t *least_edge_at(const EpicWs &ws, int64_t s) { return (uint32_t *)ws.model + 8 * s + 6; }
+__device__ __forceinline__ uint32_t least_edge(const EpicWs &ws, int64_t s) { return *least_edge_at(ws, s); }
+
+// Edge map and cleared key / adjacency tables / least edges / counters.
 __global__ void k_epic_prep(const uint8_t *I, int64_t pitch, int W, int H, int64_t n, EpicWs ws)
 {
     const uint32_t N = (uint32_t)W * (uint32_t)H;
@@ -112,7 +117,8 @@ __global__ void k_epic_prep(const uint8_t *I, int64_t pitch, int W, int H, int64
             ws.keys[i] = kNoKey;
         }
         if (i < S) ws.adj[i] = kNoKey;
-        if (i < kChunk + 2) ws.ctr[i] = i == kChunk + 1 ? 0xFFFFFFFFu : 0u;
+        if (i < n) *least_edge_at(ws, i) = kLeastCap;
+        if (i < kChunk + 2) ws.ctr[i] = 0u;
     }
 }
 
@@ -394,29 +400,30 @@ __device__ void adj_insert(const EpicWs &ws, uint32_t s, uint32_t t, uint32_t w,
     atomicOr(err, kErrDegree);
 }
 
+// Least value over the wavefront, returned to every lane (DPP and row swaps, as the sums).
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t w = __shfl_xor(v, o, 64);
-        v = w < v ? w : v;
-    }
-    return v;
+    v = min(v, dppu<0xB1>(v));
+    v = min(v, dppu<0x4E>(v));
+    v = min(v, dppu<0x141>(v));
+    v = min(v, dppu<0x140>(v));
+    const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = min((uint32_t)p[0], (uint32_t)p[1]);
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return min((uint32_t)r[0], (uint32_t)r[1]);
 }
 
 // Seed graph: every right / down pixel pair whose cells differ gives both cells an edge of
 // length D(p) + step(p, q) + D(q); each row keeps the least length per neighbour.  Neighbouring
 // lanes hold neighbouring pixels of a row, so runs of lanes often carry the same cell pair (a
 // horizontal cell border seen by the down pairs): the first lane of each run inserts the run's
-// least length for all of it.  Also the least edge length of the whole graph (one atomic per
-// wavefront).
+// least length for all of it.  Every insertion also lowers the two seeds' least edges.
 __global__ void k_epic_graph(int W, int H, int kappa, const uint64_t *keys, const uint16_t *E, EpicWs ws,
-                             uint32_t *err, uint32_t *min_edge, const uint32_t *unsettled)
+                             uint32_t *err, const uint32_t *unsettled)
 {
     if (unsettled && *unsettled) return; // the partition did not reach its fixed point
     const uint32_t N = (uint32_t)W * (uint32_t)H;
     const int lane = threadIdx.x & 63;
-    uint32_t wmin = 0xFFFFFFFFu;
     // (the loop runs a whole wavefront at a time: blockDim and the stride are multiples of 64)
     for (uint32_t base = blockIdx.x * blockDim.x + (threadIdx.x & ~63u); base < N; base += gridDim.x * blockDim.x) {
         const uint32_t p = base + lane;
@@ -449,14 +456,13 @@ __global__ void k_epic_graph(int W, int H, int kappa, const uint64_t *keys, cons
             const uint64_t prev = __shfl_up(pair, 1, 64);
             const bool head = edge && (lane == 0 || prev != pair);
             if (head) {
-                wmin = wr < wmin ? wr : wmin;
+                atomicMin(least_edge_at(ws, ls), wr);
+                atomicMin(least_edge_at(ws, lt), wr);
                 adj_insert(ws, ls, lt, wr, err);
                 adj_insert(ws, lt, ls, wr, err);
             }
         }
     }
-    wmin = wave_min_u32(wmin);
-    if (lane == 0 && wmin != 0xFFFFFFFFu) atomicMin(min_edge, wmin);
 }
 
 struct EpicFit {
@@ -471,189 +477,248 @@ struct EpicFit {
     uint32_t *nbr_dist;
     float *model_out;
     uint32_t *err;
-    const uint32_t *min_edge;
     const uint32_t *unsettled; // nullable: nonzero when the partition did not reach its fixed point
 };
 
+// Sum over the wavefront, returned to every lane: DPP butterflies inside rows of 16 lanes, then the
+// row-swap permutes (a shuffle through LDS costs several times the latency, and the fit below is a
+// chain of about twenty such sums).
+template <int CTRL>
+__device__ __forceinline__ double dppd(double v)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, (uint64_t)dppu<CTRL>((unsigned)u) | ((uint64_t)dppu<CTRL>((unsigned)(u >> 32)) << 32));
+}
+
 __device__ __forceinline__ double wave_sum_f64(double v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    v += dppd<0xB1>(v);
+    v += dppd<0x4E>(v);
+    v += dppd<0x141>(v);
+    v += dppd<0x140>(v);
+    auto halves = [](double x, auto swap) {
+        const uint64_t u = __builtin_bit_cast(uint64_t, x);
+        const auto lo = swap((unsigned)u), hi = swap((unsigned)(u >> 32));
+        return __builtin_bit_cast(double, (uint64_t)(unsigned)lo[0] | ((uint64_t)(unsigned)hi[0] << 32)) +
+               __builtin_bit_cast(double, (uint64_t)(unsigned)lo[1] | ((uint64_t)(unsigned)hi[1] << 32));
+    };
+    v = halves(v, [](unsigned x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+    return halves(v, [](unsigned x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
 }
 
 __device__ __forceinline__ int hash_slot(int32_t t) { return (int)(((uint32_t)t * 2654435761u) >> 23); }
 
 // One wavefront per seed s: its k nearest seeds on the seed graph in increasing (distance, index)
 // order, at graph distance <= 64 h, then the weighted least-squares affine model of the flow
-// around s, in FP64.  The search settles in batches (Dijkstra with buckets as wide as the least
-// edge length D of the graph): with dmin the least tentative distance of the frontier, every
-// frontier node below dmin + D is final, since any other path to it leaves the settled set
-// through a frontier node and adds at least D.  After each batch the settled set is exactly the
-// nodes below dmin + D, so once it holds k nodes its k smallest are the answer.  Candidates, a
-// hash index from node to candidate slot and the settled candidates' slots (16-bit) live in LDS:
-// 9.3 KB per search, so 17 searches share a CU.
+// around s, in FP64.  The search settles in batches: with T the least tentative distance plus
+// least outgoing edge length over the frontier, every frontier node below T is final, since any
+// other path to it leaves the settled set through some frontier node u and adds at least u's least
+// edge.  After each batch the settled set is exactly the nodes below T, so once it holds k nodes
+// its k smallest are the answer.  (With the least edge of the whole graph in place of each node's
+// own, k = 128 took 28 - 30 batches instead of 14 - 15 on driving frames.)  A batch's adjacency
+// rows are read eight lanes to a node, eight slots each; 97 % of the nodes have at most eight
+// neighbours, and the rest take further rounds.  RPL: rows of the fit per lane, k <= 64 RPL.
+//
+// The search is a chain of short LDS and L2 round trips with VALU and scalar issue about even between
+// them: LDS is kept to 6.9 KB so that 21 searches share a CU, edges are inserted 64 at a time, nodes
+// are ranked within their batch only, and the fit's first column comes from the moments.  2048x1024,
+// 117,238 seeds, k 128: 2,382 -> 1,026 us (7,185 -> 3,510 VALU and 5,000 -> 2,850 scalar instructions
+// per seed); 1242x375, 9,368 seeds: 246 -> 116 us.  Candidate capacity and results are as before.
+template <int RPL>
 __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
 {
     if (F.unsettled && *F.unsettled) return; // the partition did not reach its fixed point
     static_assert(kHash == 1 << 9, "hash_slot returns 9 bits");
-    constexpr int kStageNodes = 8; // batch nodes whose adjacency rows are read together
-    static_assert(kStageNodes * kMaxDeg >= kMaxK, "the sorted output reuses the staging arrays");
-    __shared__ int32_t hkey[kHash];
-    __shared__ int16_t hval[kHash];
-    __shared__ int32_t cid[kCand];
-    __shared__ uint32_t cdist[kCand];
-    __shared__ uint8_t cdone[kCand];
-    __shared__ int16_t sslot[kCand]; // candidate slots of the settled nodes, in settling order
-    __shared__ int32_t it_t[kStageNodes * kMaxDeg];
-    __shared__ uint32_t it_c[kStageNodes * kMaxDeg];
-    int32_t *oid = it_t; // the k nearest, sorted (after the search, over the staging arrays)
-    uint32_t *od = it_c;
+    static_assert(kHash >= 2 * kMaxK, "the sorted output reuses the hash keys");
+    constexpr int kChunks = (kCand + 63) / 64;
+    __shared__ int32_t hkey[kHash];   // node, or -1
+    __shared__ uint16_t hval[kHash];  // its candidate slot
+    __shared__ uint32_t cdist[kCand]; // candidates: tentative distance (all ones past the last one),
+    __shared__ uint16_t chash[kCand]; // place in the hash,
+    __shared__ uint16_t cmin[kCand];  // and least edge, in units of 2^shift (rounded down)
+    __shared__ uint16_t sslot[kCand]; // candidate slots of the settled nodes, sorted by (distance, index)
     const int li = threadIdx.x;
-    const uint64_t below = (1ull << li) - 1ull;
     const int64_t s = blockIdx.x;
     if (s >= F.n) return; // whole wave
 
     uint32_t q = 0;
     bool alive = seed_pixel(F.pts, F.flow, F.status, s, F.W, F.H, q);
     if (alive) alive = F.keys[q] == (uint64_t)s; // s owns its pixel at distance 0
+    // (every branch of the search is the wavefront's: the read-first-lanes keep its state in scalar
+    // registers and the control flow free of execution masks)
+    alive = __builtin_amdgcn_readfirstlane(alive ? 1 : 0) != 0;
+    auto before = [](uint64_t mask) { // set bits of the mask in lower lanes
+        return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+    };
+    auto node_of = [&](int slot) { return hkey[chash[slot]]; };
     int cnt = 0;
     bool overflow = false;
     if (alive) {
         for (int j = li; j < kHash; j += 64) hkey[j] = -1;
+        for (int j = li; j < kCand; j += 64) cdist[j] = 0xFFFFFFFFu;
         __syncthreads();
         if (li == 0) {
-            hkey[hash_slot((int32_t)s)] = (int32_t)s;
-            hval[hash_slot((int32_t)s)] = 0;
-            cid[0] = (int32_t)s;
+            const int h = hash_slot((int32_t)s);
+            hkey[h] = (int32_t)s;
+            hval[h] = 0;
+            chash[0] = (uint16_t)h;
             cdist[0] = 0u;
-            cdone[0] = 0;
+            cmin[0] = 0; // (alone in its batch whatever T is)
         }
-        int m = 1;
-        const uint64_t bucket = *F.min_edge; // >= kappa >= 1 (all ones when there is no edge)
+        // a least edge beyond dmax bounds no more than dmax does, so 16 bits of dmax's scale hold it
+        const int shift = max(0, 16 - __builtin_clz(F.dmax | 1u));
+        const uint32_t least_cap = min(F.dmax >> shift, 0xFFFFu);
+        int m = 1, first = 0;  // candidates, and the first group of 64 that are not all settled (its slot)
+        uint32_t settled = 0u; // nodes below this distance are settled
         __syncthreads();
         for (;;) {
-            uint32_t lmin = 0xFFFFFFFFu;
-            for (int j = li; j < m; j += 64)
-                if (!cdone[j]) lmin = cdist[j] < lmin ? cdist[j] : lmin;
-            const uint32_t dmin = wave_min_u32(lmin);
-            if (dmin == 0xFFFFFFFFu) break; // frontier empty
-            const uint64_t T = (uint64_t)dmin + bucket;
+            // T (distances and least edges are at most dmax <= 2^30, so sums fit)
+            uint32_t T = 0xFFFFFFFFu;
+            for (int base = first; base < m; base += 64) {
+                const uint32_t d = cdist[base + li], least = max((uint32_t)cmin[base + li] << shift, 1u);
+                if (d - settled < 0xFFFFFFFFu - settled) T = min(T, d + least); // settled <= d < all ones
+            }
+            T = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_min_u32(T));
+            if (T == 0xFFFFFFFFu) break; // frontier empty
+            // the batch
             const int b0 = cnt;
-            for (int base = 0; base < m; base += 64) {
-                const int j = base + li;
-                const bool sel = j < m && !cdone[j] && (uint64_t)cdist[j] < T;
+            int head = first;
+            for (int base = first; base < m; base += 64) {
+                const uint32_t d = cdist[base + li];
+                const bool sel = d - settled < T - settled; // settled <= d < T
                 const uint64_t bm = __ballot(sel);
-                if (sel) {
-                    sslot[cnt + __popcll(bm & below)] = (int16_t)j;
-                    cdone[j] = 1;
-                }
+                if (sel) sslot[cnt + before(bm)] = (uint16_t)(base + li);
                 cnt += __popcll(bm);
+                if (head == base && base + 64 <= m && __ballot(d >= T) == 0ull) head = base + 64;
+            }
+            first = head;
+            settled = T;
+            __syncthreads();
+            // sort it by (distance, index)
+            const int nb = cnt - b0;
+            int32_t id = 0; // lane i: the batch's i-th node, before sorting
+            uint32_t nd = 0u;
+            if (nb <= 64) {
+                int slot = 0, rank = 0;
+                if (li < nb) {
+                    slot = sslot[b0 + li];
+                    nd = cdist[slot];
+                    id = node_of(slot);
+                }
+                const uint64_t key = ((uint64_t)nd << 32) | (uint32_t)id;
+                for (int i = 0; i < nb; ++i) {
+                    const uint64_t other = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)nd, i) << 32) |
+                                           (uint32_t)__builtin_amdgcn_readlane(id, i);
+                    rank += other < key;
+                }
+                if (li < nb) sslot[b0 + rank] = (uint16_t)slot;
+            } else { // (many nodes at equal distances)
+                int slot[kChunks], rank[kChunks];
+#pragma unroll
+                for (int c = 0; c < kChunks; ++c) {
+                    slot[c] = rank[c] = 0;
+                    if (64 * c + li < nb) {
+                        slot[c] = sslot[b0 + 64 * c + li];
+                        const uint64_t key = ((uint64_t)cdist[slot[c]] << 32) | (uint32_t)node_of(slot[c]);
+                        for (int i = 0; i < nb; ++i) {
+                            const int other = sslot[b0 + i];
+                            rank[c] += (((uint64_t)cdist[other] << 32) | (uint32_t)node_of(other)) < key;
+                        }
+                    }
+                }
+                __syncthreads();
+#pragma unroll
+                for (int c = 0; c < kChunks; ++c)
+                    if (64 * c + li < nb) sslot[b0 + rank[c]] = (uint16_t)slot[c];
             }
             __syncthreads();
             if (cnt >= F.k) break;
-            // relax the batch's edges, kStageNodes adjacency rows at a time
-            for (int nb0 = b0; nb0 < cnt && !overflow; nb0 += kStageNodes) {
-                const int nn = cnt - nb0 < kStageNodes ? cnt - nb0 : kStageNodes;
-                uint64_t e[kStageNodes * kMaxDeg / 64];
-                uint32_t dv[kStageNodes * kMaxDeg / 64];
-#pragma unroll
-                for (int r = 0; r < kStageNodes * kMaxDeg / 64; ++r) {
-                    const int idx = li + 64 * r, node = idx / kMaxDeg, slot = idx - node * kMaxDeg;
-                    e[r] = kNoKey;
-                    dv[r] = 0u;
-                    if (node < nn) {
-                        const int cs = sslot[nb0 + node];
-                        e[r] = F.ws.adj[(int64_t)cid[cs] * kMaxDeg + slot];
-                        dv[r] = cdist[cs];
+            // Relax the batch's edges.  Rows are read eight lanes to a node (they fill from slot 0; the
+            // few nodes with more than eight neighbours are read again), and the edges found are
+            // queued, one per lane, so that the insertion below runs once per 64 edges.
+            int32_t qt = 0;
+            uint32_t qc = 0u;
+            int queued = 0;
+            auto insert = [&]() {
+                const bool ok = li < queued;
+                uint32_t least = 0u;
+                if (ok) least = least_edge(F.ws, qt); // in flight during the probing
+                // find or claim the node's place (the table is never full: at most kCand + 64 of kHash)
+                int hs = hash_slot(qt);
+                bool is_new = false, open = ok;
+                while (__ballot(open) != 0ull) {
+                    if (open) {
+                        const int32_t old = atomicCAS(&hkey[hs], -1, qt);
+                        is_new = old == -1;
+                        open = !is_new && old != qt;
+                        if (open) hs = (hs + 1) & (kHash - 1);
                     }
                 }
-                int ni = 0;
-#pragma unroll
-                for (int r = 0; r < kStageNodes * kMaxDeg / 64; ++r) {
-                    const uint64_t c64 = e[r] == kNoKey ? ~0ull : (uint64_t)dv[r] + (e[r] >> 32);
-                    const bool ok = c64 <= F.dmax;
-                    const uint64_t bm = __ballot(ok);
-                    if (ok) {
-                        const int at = ni + __popcll(bm & below);
-                        it_t[at] = (int32_t)(uint32_t)e[r];
-                        it_c[at] = (uint32_t)c64;
-                    }
-                    ni += __popcll(bm);
+                queued = 0;
+                const uint64_t nbm = __ballot(is_new);
+                const int total = __popcll(nbm);
+                if (m + total > kCand) {
+                    overflow = true;
+                    return;
                 }
+                if (is_new) {
+                    const int slot = m + before(nbm);
+                    hval[hs] = (uint16_t)slot;
+                    chash[slot] = (uint16_t)hs;
+                    cmin[slot] = (uint16_t)min(least >> shift, least_cap);
+                }
+                m += total;
                 __syncthreads();
-                for (int ib = 0; ib < ni; ib += 64) {
-                    const int i = ib + li;
-                    const bool has = i < ni;
-                    int32_t t = -1;
-                    uint32_t c = 0u;
-                    int hpos = -1;
-                    bool is_new = false;
-                    if (has) {
-                        t = it_t[i];
-                        c = it_c[i];
-                        int hs = hash_slot(t);
-                        for (int probe = 0; probe < kHash; ++probe) {
-                            const int32_t old = atomicCAS(&hkey[hs], -1, t);
-                            if (old == -1 || old == t) {
-                                hpos = hs;
-                                is_new = old == -1;
-                                break;
-                            }
-                            hs = (hs + 1) & (kHash - 1);
-                        }
-                    }
-                    __syncthreads();
-                    const uint64_t nbm = __ballot(is_new);
-                    const int total = __popcll(nbm);
-                    if (m + total > kCand) {
-                        overflow = true;
-                        break;
-                    }
-                    if (is_new) {
-                        const int slot = m + __popcll(nbm & below);
-                        hval[hpos] = (int16_t)slot;
-                        cid[slot] = t;
-                        cdist[slot] = 0xFFFFFFFFu;
-                        cdone[slot] = 0;
-                    }
-                    m += total;
-                    __syncthreads();
-                    if (hpos >= 0) {
-                        const int slot = hval[hpos];
-                        if (!cdone[slot]) atomicMin(&cdist[slot], c);
-                    }
-                    __syncthreads();
+                // (a settled node's distance is below T, which no path through this batch is)
+                if (ok) atomicMin(&cdist[hval[hs]], qc);
+                __syncthreads();
+            };
+            for (int n0 = 0; n0 < nb && !overflow; n0 += 8) {
+                const int ni = n0 + (li >> 3);
+                const bool on = ni < nb;
+                int32_t node;
+                uint32_t dv;
+                if (nb <= 64) { // (the batch in lane order; any order gives the same distances)
+                    node = __builtin_amdgcn_ds_bpermute(4 * ni, id);
+                    dv = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * ni, (int)nd);
+                } else {
+                    const int slot = sslot[b0 + min(ni, nb - 1)];
+                    node = node_of(slot);
+                    dv = cdist[slot];
+                }
+                const uint64_t *row = F.ws.adj + (int64_t)node * kMaxDeg + (li & 7);
+                for (int s0 = 0; s0 < kMaxDeg && !overflow; s0 += 8) {
+                    const uint64_t e = on ? row[s0] : kNoKey;
+                    const uint64_t c64 = (uint64_t)dv + (e >> 32);
+                    const bool ok = e != kNoKey && c64 <= F.dmax;
+                    const uint64_t bm = __ballot(ok);
+                    const int n = __popcll(bm);
+                    if (queued + n > 64) insert();
+                    // the queue lane each edge goes to; the other lanes fill the rest of a permutation
+                    const int rank = before(bm);
+                    const int to = 4 * ((ok ? queued + rank : queued + n + li - rank) & 63);
+                    const int32_t t = __builtin_amdgcn_ds_permute(to, (int32_t)(uint32_t)e);
+                    const int32_t c = __builtin_amdgcn_ds_permute(to, (int32_t)(uint32_t)c64);
+                    const bool mine = li >= queued && li < queued + n;
+                    qt = mine ? t : qt;
+                    qc = mine ? (uint32_t)c : qc;
+                    queued += n;
+                    // a full eighth slot: there may be more
+                    if (__ballot((li & 7) == 7 && e != kNoKey) == 0ull) break;
                 }
             }
+            if (queued > 0 && !overflow) insert();
             if (overflow) break;
         }
         __syncthreads();
-        if (!overflow) {
-            // the k smallest settled (distance, index) pairs, by rank
-            for (int j = li; j < cnt; j += 64) {
-                const int cj = sslot[j];
-                const uint64_t kj = ((uint64_t)cdist[cj] << 32) | (uint32_t)cid[cj];
-                int rank = 0;
-                for (int i = 0; i < cnt; ++i) {
-                    const int ci = sslot[i];
-                    rank += (((uint64_t)cdist[ci] << 32) | (uint32_t)cid[ci]) < kj;
-                }
-                if (rank < F.k) {
-                    oid[rank] = cid[cj];
-                    od[rank] = cdist[cj];
-                }
-            }
-            cnt = cnt < F.k ? cnt : F.k;
-        }
-        __syncthreads();
+        cnt = cnt < F.k ? cnt : F.k;
     }
     if (overflow && li == 0) atomicOr(F.err, kErrCand);
     if (!alive || overflow) cnt = 0;
     if (F.nbr)
         for (int j = li; j < F.k; j += 64) {
-            F.nbr[s * F.k + j] = j < cnt ? oid[j] : -1;
-            F.nbr_dist[s * F.k + j] = j < cnt ? od[j] : 0xFFFFFFFFu;
+            F.nbr[s * F.k + j] = j < cnt ? node_of(sslot[j]) : -1;
+            F.nbr_dist[s * F.k + j] = j < cnt ? cdist[sslot[j]] : 0xFFFFFFFFu;
         }
     float *mo = F.ws.model + 8 * s;
     if (!alive || overflow) {
@@ -664,40 +729,40 @@ __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
         return;
     }
     // weighted position moments about the seed's own position (for the degeneracy test)
-    constexpr int RPL = kMaxK / 64; // rows per lane
     const double sx = F.pts[2 * s], sy = F.pts[2 * s + 1];
     double c1[RPL], cx[RPL], cy[RPL], bu[RPL], bv[RPL]; // sqrt(w) (1, x, y | u, v)
     double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};              // w, x, y, xx, xy, yy, u, v
+    const double half = -0.5 / (double)F.h;
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
         const int j = li + 64 * r;
         c1[r] = cx[r] = cy[r] = bu[r] = bv[r] = 0.0;
         if (j < cnt) {
-            const int32_t t = oid[j];
-            const double w = exp2(-(double)od[j] / (double)F.h);
-            const double x = (double)F.pts[2 * t] - sx, y = (double)F.pts[2 * t + 1] - sy;
-            const double u = F.flow[2 * t], v = F.flow[2 * t + 1];
-            a[0] += w;
-            a[1] += w * x;
-            a[2] += w * y;
-            a[3] += w * x * x;
-            a[4] += w * x * y;
-            a[5] += w * y * y;
-            a[6] += w * u;
-            a[7] += w * v;
-            const double rw = sqrt(w);
+            const int slot = sslot[j];
+            const int32_t t = node_of(slot);
+            const double x = (double)F.pts[2 * (int64_t)t] - sx, y = (double)F.pts[2 * (int64_t)t + 1] - sy;
+            const double u = F.flow[2 * (int64_t)t], v = F.flow[2 * (int64_t)t + 1];
+            const double rw = exp2((double)cdist[slot] * half); // sqrt(w), w = 2^(-distance / h)
             c1[r] = rw;
             cx[r] = rw * x;
             cy[r] = rw * y;
             bu[r] = rw * u;
             bv[r] = rw * v;
+            a[0] += rw * rw;
+            a[1] += rw * cx[r];
+            a[2] += rw * cy[r];
+            a[3] += cx[r] * cx[r];
+            a[4] += cx[r] * cy[r];
+            a[5] += cy[r] * cy[r];
+            a[6] += rw * bu[r];
+            a[7] += rw * bv[r];
         }
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) a[e] = wave_sum_f64(a[e]);
     double mdl[6];
-    const double sw = a[0], ex = a[1] / sw, ey = a[2] / sw;
-    const double cxx = a[3] / sw - ex * ex, cyy = a[5] / sw - ey * ey, cxy = a[4] / sw - ex * ey;
+    const double sw = a[0], isw = 1.0 / sw, ex = a[1] * isw, ey = a[2] * isw;
+    const double cxx = a[3] * isw - ex * ex, cyy = a[5] * isw - ey * ey, cxy = a[4] * isw - ex * ey;
     const double tr = cxx + cyy, det = cxx * cyy - cxy * cxy;
     if (cnt < 3 || !(det > 1e-4 * tr * tr)) {
         mdl[0] = mdl[1] = mdl[3] = mdl[4] = 0.0;
@@ -706,7 +771,9 @@ __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
     } else {
         // weighted least squares by modified Gram-Schmidt on the columns sqrt(w) (1, x, y), the
         // right-hand sides carried along as further columns (backward stable for least squares;
-        // the weights can span 64 binades, beyond what the normal equations resolve)
+        // the weights can span 64 binades, beyond what the normal equations resolve).  The first
+        // column's products are the moments above; the columns stay unnormalised, so that each of
+        // the other two takes one round of sums: R's rows are (sw, a1, a2), (d22, d23), (d33).
         auto dot = [&](const double *p, const double *q) {
             double acc = 0.0;
 #pragma unroll
@@ -717,47 +784,35 @@ __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
 #pragma unroll
             for (int r = 0; r < RPL; ++r) p[r] -= f * q[r];
         };
-        auto scale = [&](double f, double *p) {
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) p[r] *= f;
-        };
-        const double r11 = sqrt(dot(c1, c1));
-        scale(1.0 / r11, c1);
-        const double r12 = dot(c1, cx), r13 = dot(c1, cy), z1u = dot(c1, bu), z1v = dot(c1, bv);
-        axpy(r12, c1, cx);
-        axpy(r13, c1, cy);
-        axpy(z1u, c1, bu);
-        axpy(z1v, c1, bv);
-        const double r22 = sqrt(dot(cx, cx));
-        scale(1.0 / r22, cx);
-        const double r23 = dot(cx, cy), z2u = dot(cx, bu), z2v = dot(cx, bv);
-        axpy(r23, cx, cy);
-        axpy(z2u, cx, bu);
-        axpy(z2v, cx, bv);
-        const double r33 = sqrt(dot(cy, cy));
-        scale(1.0 / r33, cy);
-        const double z3u = dot(cy, bu), z3v = dot(cy, bv);
-        // R (offset, d/dx, d/dy)^T = z
-        const double gyu = z3u / r33, gyv = z3v / r33;
-        const double gxu = (z2u - r23 * gyu) / r22, gxv = (z2v - r23 * gyv) / r22;
+        const double mu = a[6] * isw, mv = a[7] * isw;
+        axpy(ex, c1, cx);
+        axpy(ey, c1, cy);
+        axpy(mu, c1, bu);
+        axpy(mv, c1, bv);
+        const double d22 = dot(cx, cx), d23 = dot(cx, cy), d2u = dot(cx, bu), d2v = dot(cx, bv);
+        const double i22 = 1.0 / d22, f23 = d23 * i22;
+        axpy(f23, cx, cy);
+        axpy(d2u * i22, cx, bu);
+        axpy(d2v * i22, cx, bv);
+        const double d33 = dot(cy, cy), d3u = dot(cy, bu), d3v = dot(cy, bv);
+        const double gyu = d3u / d33, gyv = d3v / d33;
+        const double gxu = d2u * i22 - f23 * gyu, gxv = d2v * i22 - f23 * gyv;
         mdl[0] = gxu;
         mdl[1] = gyu;
-        mdl[2] = (z1u - r12 * gxu - r13 * gyu) / r11;
+        mdl[2] = mu - ex * gxu - ey * gyu;
         mdl[3] = gxv;
         mdl[4] = gyv;
-        mdl[5] = (z1v - r12 * gxv - r13 * gyv) / r11;
+        mdl[5] = mv - ex * gxv - ey * gyv;
     }
     if (li != 0) return;
     for (int e = 0; e < 6; ++e) {
         mo[e] = (float)mdl[e];
         if (F.model_out) F.model_out[6 * s + e] = (float)mdl[e];
     }
-    mo[6] = (float)sx;
-    mo[7] = (float)sy;
 }
 
 // Every pixel evaluates the model of its cell's seed at its own coordinates.
-__global__ void k_epic_dense(int W, int H, const uint64_t *keys, const float *model, float *dense, int64_t dpitch,
+__global__ void k_epic_dense(int W, int H, const uint64_t *keys, const float *model, const float *pts, float *dense, int64_t dpitch,
                              int32_t *labels, uint32_t *dist, const uint32_t *unsettled)
 {
     if (unsettled && *unsettled) return; // the partition did not reach its fixed point
@@ -771,7 +826,8 @@ __global__ void k_epic_dense(int W, int H, const uint64_t *keys, const float *mo
         } else {
             const float4 *m = reinterpret_cast<const float4 *>(model + 8 * (int64_t)(uint32_t)k);
             const float4 m0 = m[0], m1 = m[1];
-            const float rx = (float)x - m1.z, ry = (float)y - m1.w;
+            const float *at = pts + 2 * (int64_t)(uint32_t)k;
+            const float rx = (float)x - at[0], ry = (float)y - at[1];
             f = make_float2(fmaf(m0.x, rx, fmaf(m0.y, ry, m0.z)), fmaf(m0.w, rx, fmaf(m1.x, ry, m1.y)));
         }
         *reinterpret_cast<float2 *>(dense + (int64_t)y * dpitch + 2 * x) = f;
@@ -909,7 +965,7 @@ int epic_run(const dgf_image *I0, const float *points, const float *flow, const 
         if (sync && !converged) return DGF_ERR_UNSUPPORTED;
         unsettled = sync ? nullptr : ws.ctr + last;
         hipLaunchKernelGGL(k_epic_graph, dim3(grid_for(N, 256)), dim3(256), 0, st, W, H, o.kappa,
-                           (const uint64_t *)ws.keys, (const uint16_t *)ws.E, ws, err, ws.ctr + kChunk + 1, unsettled);
+                           (const uint64_t *)ws.keys, (const uint16_t *)ws.E, ws, err, unsettled);
         if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
         EpicFit F{};
         F.pts = points;
@@ -927,13 +983,15 @@ int epic_run(const dgf_image *I0, const float *points, const float *flow, const 
         F.nbr_dist = nbr_dist;
         F.model_out = model;
         F.err = err;
-        F.min_edge = ws.ctr + kChunk + 1;
         F.unsettled = unsettled;
-        hipLaunchKernelGGL(k_epic_knn_fit, dim3((unsigned)n), dim3(64), 0, st, F);
+        if (o.k <= 128)
+            hipLaunchKernelGGL(k_epic_knn_fit<2>, dim3((unsigned)n), dim3(64), 0, st, F);
+        else
+            hipLaunchKernelGGL(k_epic_knn_fit<kMaxK / 64>, dim3((unsigned)n), dim3(64), 0, st, F);
         if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
     }
     hipLaunchKernelGGL(k_epic_dense, dim3(grid_for(N, 256)), dim3(256), 0, st, W, H, (const uint64_t *)ws.keys,
-                       (const float *)ws.model, dense, dense_pitch, labels, dist, unsettled);
+                       (const float *)ws.model, points, dense, dense_pitch, labels, dist, unsettled);
     if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
     if (max_relax > 0) {
         hipLaunchKernelGGL(k_epic_status, dim3(1), dim3(1), 0, st, status_out, unsettled, (const uint32_t *)err);
