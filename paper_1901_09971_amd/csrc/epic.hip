@@ -9,10 +9,9 @@
 // GPU structure (one pass each unless noted):
 //   k_epic_prep     edge map (uint16) and cleared tables, HBM bound
 //   k_epic_seed     one 64-bit atomicMin per converged point: key = (0 << 32) | index
-//   k_epic_relax    32x64 tiles relaxed in LDS (Bellman-Ford sweeps over the tile, double
-//                   buffered), exchanging border pixels with their neighbours through 64-bit
-//                   atomics during the launch; launched until a launch changes nothing (host
-//                   checks a counter every few launches: the one synchronisation of the call)
+//   k_epic_relax    62x32 tiles relaxed in registers (Bellman-Ford sweeps), exchanging border
+//                   pixels with their neighbours during the launch; launched until a launch
+//                   changes nothing (host checks a counter every few launches)
 //   k_epic_graph    adjacent-cell pairs inserted into fixed-size per-seed adjacency rows
 //   k_epic_knn_fit  one wavefront per seed: Dijkstra on the seed graph with the frontier and a
 //                   hash index in LDS, stopped after k settles; FP64 weighted affine fit by
@@ -23,6 +22,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "dgf_internal.hpp"
 
 namespace dgf {
@@ -32,21 +33,24 @@ constexpr int kMaxDeg = 32;          // graph neighbours a seed can hold
 constexpr int kCand = 384;           // candidates one neighbour search can hold (about 210 needed at k 128)
 constexpr int kHash = 512;           // LDS hash slots of one search (power of two, > kCand + kMaxDeg)
 constexpr int kMaxK = 256;           // largest k
-// relaxation tile: 32 x 64 crossed fewer tile borders than 32 x 32 on the benchmark frames
-// (0.755 against 0.792 ms per 1242x375 frame); 64 x 64 tiles put 16 wavefronts behind each
-// barrier and were slower (0.816 ms)
-constexpr int kRTX = 32;             // relaxation tile width
-constexpr int kRTY = 64;             // relaxation tile height
-constexpr int kRTX2 = kRTX + 2;      // with the halo
-constexpr int kRTY2 = kRTY + 2;
-constexpr int kRelaxThreads = kRTX * kRTY / 4; // each lane owns 4 pixels of one column
-static_assert(kRelaxThreads % 64 == 0 && kRelaxThreads <= 1024 && kRTY % (kRelaxThreads / kRTX) == 0, "tile shape");
-constexpr int kExchange = 32;        // relaxation iterations between two halo exchanges
-constexpr int kMaxIters = 8192;      // relaxation iterations per tile and launch
+// Relaxation tile: a wavefront holds 64 columns, the outer two of them the neighbouring tiles', and
+// kRRows rows of them, one column's run per lane; kRWaves wavefronts stack up.  The 1242x375 frame
+// then has 252 tiles, one per CU.
+constexpr int kRTX = 62;             // tile width
+constexpr int kRRows = 8;            // rows per wavefront
+constexpr int kRWaves = 4;
+constexpr int kRTY = kRWaves * kRRows; // tile height
+constexpr int kRelaxThreads = 64 * kRWaves;
+constexpr int kInner = 4;            // relaxation iterations of a round, between two checks for changes
+constexpr int kExchange = 8;         // rounds between two halo exchanges
+constexpr int kMaxRounds = 2048;     // rounds per tile and launch
 constexpr int kMaxPolls = 4096;      // halo polls of a still tile per launch
-constexpr int kChunk = 4;            // relaxation launches between two convergence checks
+constexpr int kPollSleep = 2;        // 64-cycle units between two polls
+constexpr int kStartPolls = 256;     // polls a resident grid waits for tiles that have not started
+constexpr int kChunk = 4;            // relaxation launches between two convergence checks, and sets of their counters
 constexpr int kMaxRelaxLaunches = 1 << 14;
 constexpr int kDefaultAsyncRelax = 32; // dgf_epic_async's relaxation launches when given 0
+constexpr int kRestBlocks = 128;     // workgroups of the launches after a resident grid's second
 constexpr uint64_t kNoKey = ~0ull;
 constexpr uint64_t kDistCap = 0xFFFFFFFEull;
 constexpr int kMaxEdge = 510;        // largest edge-map value
@@ -59,10 +63,11 @@ struct EpicWs {
     uint16_t *E;     // [H*W]
     uint64_t *adj;   // [n][kMaxDeg]: (edge length << 32) | neighbour, kNoKey = empty slot
     float *model;    // [n][8]: affine coefficients (6), least edge of the seed (uint32 bits), unused
-    uint32_t *ctr;   // [kChunk] tiles changed per relaxation launch, [1] error bits, [1] unused,
-                     // [kChunk] busy count per relaxation launch, [1] the changed count of the
-                     // launch before the current group of kChunk
+    uint32_t *ctr;   // [kChunk] tiles changed by a relaxation launch, [1] error bits, [kChunk] open
+                     // count and [kChunk] done flag of a relaxation launch (launch j uses set
+                     // j mod kChunk of these, of mail and of state)
     uint32_t *mail;  // [kChunk][tiles]: a neighbour published keys into this tile's halo
+    uint32_t *state; // [kChunk][tiles]: 0 before the tile starts, then 4 x times resumed + 2, + 1 while still
 };
 
 int64_t align256(int64_t v) { return (v + 255) / 256 * 256; }
@@ -78,7 +83,7 @@ int64_t ws_layout(int W, int H, int64_t n, EpicWs *ws, char *base)
     };
     char *keys = take(8 * N), *E = take(2 * N), *adj = take(8 * n * kMaxDeg);
     const int64_t tiles = (int64_t)((W + kRTX - 1) / kRTX) * ((H + kRTY - 1) / kRTY);
-    char *model = take(32 * n), *ctr = take(4 * (2 * kChunk + 3)), *mail = take(4 * kChunk * tiles);
+    char *model = take(32 * n), *ctr = take(4 * (3 * kChunk + 1)), *mail = take(8 * kChunk * tiles);
     if (ws) {
         ws->keys = (uint64_t *)keys;
         ws->E = (uint16_t *)E;
@@ -86,6 +91,7 @@ int64_t ws_layout(int W, int H, int64_t n, EpicWs *ws, char *base)
         ws->model = (float *)model;
         ws->ctr = (uint32_t *)ctr;
         ws->mail = (uint32_t *)mail;
+        ws->state = ws->mail + kChunk * tiles;
     }
     return off;
 }
@@ -95,16 +101,31 @@ __device__ __forceinline__ uint64_t load_key(const uint64_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ uint32_t load_word(const uint32_t *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void store_word(uint32_t *p, uint32_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void store_key(uint64_t *p, uint64_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The least edge length of a seed's row.
 __device__ __forceinline__ uint32_t *least_edge_at(const EpicWs &ws, int64_t s) { return (uint32_t *)ws.model + 8 * s + 6; }
 __device__ __forceinline__ uint32_t least_edge(const EpicWs &ws, int64_t s) { return *least_edge_at(ws, s); }
 
 // Edge map and cleared key / adjacency tables / least edges / counters.
-__global__ void k_epic_prep(const uint8_t *I, int64_t pitch, int W, int H, int64_t n, EpicWs ws)
+__global__ void k_epic_prep(const uint8_t *I, int64_t pitch, int W, int H, int64_t n, uint32_t tiles, EpicWs ws)
 {
     const uint32_t N = (uint32_t)W * (uint32_t)H;
-    const int64_t S = n * kMaxDeg;
-    const int64_t tot = S > (int64_t)N ? S : (int64_t)N;
+    const int64_t S = n * kMaxDeg, C = 2 * (int64_t)kChunk * tiles + 3 * kChunk + 1;
+    const int64_t tot = max(max(S, (int64_t)N), C);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < tot; i += (int64_t)gridDim.x * blockDim.x) {
         if (i < (int64_t)N) {
             const uint32_t q = (uint32_t)i, y = q / (uint32_t)W, x = q - y * (uint32_t)W;
@@ -118,7 +139,8 @@ __global__ void k_epic_prep(const uint8_t *I, int64_t pitch, int W, int H, int64
         }
         if (i < S) ws.adj[i] = kNoKey;
         if (i < n) *least_edge_at(ws, i) = kLeastCap;
-        if (i < kChunk + 2) ws.ctr[i] = 0u;
+        if (i <= 3 * kChunk) ws.ctr[i] = 0u;
+        if (i < 2 * (int64_t)kChunk * tiles) ws.mail[i] = 0u; // and state
     }
 }
 
@@ -145,239 +167,323 @@ __global__ void k_epic_seed(const float *pts, const float *flow, const uint8_t *
     if (seed_pixel(pts, flow, status, i, W, H, q)) atomicMin((unsigned long long *)(keys + q), (unsigned long long)i);
 }
 
-// Key of the path that reaches a pixel from a neighbour holding key kn with a step of cost c:
-// the distance half saturates at all ones, so kNoKey stays kNoKey; a saturated distance is
-// never a least one (every least distance is below kDistCap) and is replaced in time.
-__device__ __forceinline__ uint64_t step_key(uint64_t kn, uint32_t c)
+// How the relaxation handles keys.  A key is the pair (distance, seed), the least first.
+//   Fast: distances below kFar, whose keys as bit patterns are positive doubles, so that one
+//         v_min_f64 takes the lesser of two (denormals are kept in double precision).  No key is
+//         kFar in the distance half; kFar plus any step stays below the doubles' infinities.
+//   else: any distance below kDistCap, by 64-bit integer comparisons; kNoKey plus any step stays kNoKey.
+constexpr uint32_t kFar = 0x3F000000u;
+
+enum : uint32_t { kDone = 1u, kLeave = 2u };
+
+// The counters of one relaxation launch.
+struct RelaxCounters {
+    uint32_t *changed; // tiles that changed anything
+    uint32_t *open;    // tiles that left before the whole grid had settled
+    uint32_t *done;    // kDone once it has, kLeave when the still tiles are to make room
+    uint32_t *mail, *state; // [tiles]
+};
+
+RelaxCounters relax_counters(const EpicWs &ws, int launch, int64_t tiles)
 {
-    const uint32_t hi = (uint32_t)(kn >> 32);
-    uint32_t d = hi + c;
-    d = d < hi ? 0xFFFFFFFFu : d;
-    return ((uint64_t)d << 32) | (kn & 0xFFFFFFFFull);
+    const int c = launch % kChunk;
+    return {ws.ctr + c, ws.ctr + kChunk + 1 + c, ws.ctr + 2 * kChunk + 1 + c, ws.mail + c * tiles, ws.state + c * tiles};
 }
 
-// One relaxation launch over 32x64 tiles.  Each tile holds its pixels and a one-pixel halo in
-// LDS (two buffers) and iterates key(p) = min(key(p), min over 4-neighbours q of key(q) +
-// step(q, p)) -- one barrier per iteration, each lane owning 4 pixels whose step costs stay in
-// registers.  Every kExchange iterations, and whenever it has stopped changing, a tile publishes
-// its newly improved border pixels with 64-bit atomicMin and posts mail to each neighbour tile
-// whose halo they touch; a tile with mail re-reads its halo.  Termination: `busy` counts the
-// tiles that are working plus the mail not yet taken (a publisher adds one for each mailbox it
-// fills, before it can itself go still), so it reaches zero only when no tile can change
-// anything.  A still tile (with `wait`: the whole grid resident at once) polls its mailbox and
-// the count, resuming on mail and leaving at zero; polls are bounded (kMaxPolls) so every tile
-// exits.  Keys only decrease and always belong to a real path, so any interleaving converges to
-// the exact least keys, and a launch in which no tile changes anything is at that fixed point.
-// prev (nullable): the changed count of the launch before; when it is zero the distances are
-// already at the fixed point and the launch returns at once (so a fixed number of launches can be
-// enqueued without reading anything back).
-__global__ __launch_bounds__(kRelaxThreads) void k_epic_relax(int W, int H, int kappa, uint64_t *keys,
-                                                              const uint16_t *E, uint32_t *changed, uint32_t *busy,
-                                                              uint32_t *mail, int wait, const uint32_t *prev)
+template <bool FAST>
+__device__ __forceinline__ uint64_t key_of(uint64_t k) // a stored key, as the relaxation holds it
 {
-    if (prev && *prev == 0u) return; // the same value in every block (an earlier kernel wrote it)
-    __shared__ uint64_t K[2][kRTX2 * kRTY2];
-    __shared__ uint16_t Es[kRTX2 * kRTY2];
-    __shared__ uint32_t flags[2][kRelaxThreads / 64];
-    __shared__ uint32_t sides, got_mail, count_zero;
-    const int x0 = (int)blockIdx.x * kRTX - 1, y0 = (int)blockIdx.y * kRTY - 1;
-    const int me = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-    const int nbr_tile[4] = {blockIdx.x > 0 ? me - 1 : -1, blockIdx.x + 1 < gridDim.x ? me + 1 : -1,
-                             blockIdx.y > 0 ? me - (int)gridDim.x : -1,
-                             blockIdx.y + 1 < gridDim.y ? me + (int)gridDim.x : -1};
-    // the halo ring: 2 (kRTX + 2) + 2 kRTY cells (top row, bottom row, left column, right column)
-    auto ring_cell = [&](int i) {
-        if (i < kRTX2) return i;
-        if (i < 2 * kRTX2) return (kRTY + 1) * kRTX2 + (i - kRTX2);
-        i -= 2 * kRTX2;
-        return i < kRTY ? (i + 1) * kRTX2 : (i - kRTY + 1) * kRTX2 + kRTX + 1;
-    };
-    auto global_of = [&](int c, uint32_t &q) {
-        const int ly = c / kRTX2, lx = c - ly * kRTX2;
-        const int gx = x0 + lx, gy = y0 + ly;
-        q = (uint32_t)gy * (uint32_t)W + (uint32_t)gx;
-        return gx >= 0 && gy >= 0 && gx < W && gy < H;
-    };
-    for (int c = threadIdx.x; c < kRTX2 * kRTY2; c += kRelaxThreads) {
-        uint32_t q;
-        uint64_t k = kNoKey;
-        uint16_t e = 0;
-        if (global_of(c, q)) {
-            k = load_key(keys + q);
-            e = E[q];
-        }
-        K[0][c] = k;
-        K[1][c] = k;
-        Es[c] = e;
+    return FAST && k == kNoKey ? ((uint64_t)kFar << 32) | 0xFFFFFFFFu : k;
+}
+
+template <bool FAST>
+constexpr uint32_t kWall = FAST ? kFar + 1u : 0xFFFFFFFFu; // a step nobody takes
+
+// The lesser of `mine` and `from` (a neighbour's key) after a step of cost c.
+template <bool FAST>
+__device__ __forceinline__ uint64_t key_relax(uint64_t mine, uint64_t from, uint32_t c)
+{
+    const uint32_t lo = (uint32_t)from, hi = (uint32_t)(from >> 32);
+    if constexpr (FAST) {
+        double a = __builtin_bit_cast(double, mine);
+        const double v = __builtin_bit_cast(double, ((uint64_t)(hi + c) << 32) | lo);
+        // (written out: the library's minimum would first quiet signalling NaNs, which no key is)
+        asm("v_min_f64 %0, %0, %1" : "+v"(a) : "v"(v));
+        return __builtin_bit_cast(uint64_t, a);
+    } else {
+        uint32_t d = hi + c;
+        d = d < hi ? 0xFFFFFFFFu : d;
+        const uint64_t v = ((uint64_t)d << 32) | lo;
+        return v < mine ? v : mine;
     }
+}
+
+// The key of the lane to the left / right (whole-wavefront shifts).
+template <int CTRL>
+__device__ __forceinline__ uint64_t key_shift(uint64_t k)
+{
+    auto half = [](unsigned v) { return (unsigned)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true); };
+    return (uint64_t)half((unsigned)k) | ((uint64_t)half((unsigned)(k >> 32)) << 32);
+}
+
+// One relaxation launch: key(p) = min(key(p), min over 4-neighbours q of key(q) + step(q, p)) to the
+// fixed point, over tiles of 62 x 32 pixels.  Pixels live in registers, a run of kRRows rows of one
+// column per lane.  An iteration relaxes every pixel from its left and right neighbours (the lanes
+// next to it), then down the run and up it again, so a path advances a column per iteration and any
+// number of rows inside a run; the runs' end rows are exchanged through LDS, without a barrier,
+// since keys only decrease and any interleaving converges to the same least keys.  Lanes 0 and 63
+// hold the neighbouring tiles' columns and take no part themselves (their steps cost a wall).
+// Every kInner iterations the tile looks for changes.  Every kExchange such rounds, and when it has
+// stopped changing, it publishes its changed border pixels (a pixel is only ever written by its own
+// tile) and posts mail to each neighbour tile whose halo they touch; a tile with mail re-reads its
+// halo.  With `wait` (the whole grid fits the chip at once) a still tile polls its mailbox and resumes on
+// mail; polls are bounded (kMaxPolls), so every tile exits.  Termination: a tile says in its state
+// word that it is still, after its last mail was posted, and that it is working again before it takes
+// the mail that woke it.  Tile 0, itself still, reads every state, then every mailbox and every state
+// again: all still with unchanged words means that all were still between the two readings, and with
+// every mailbox empty after that no tile can change anything any more, so it raises `done`, on
+// which every still tile leaves; where other work on the chip has kept some tiles from starting for
+// kStartPolls polls it sends the still tiles away instead, to make room.  (One count of working tiles and unread mail, kept with atomics,
+// was the bottleneck: its address took an atomic from every exchange of every tile.)  Keys always
+// belong to a real path, so a launch in which no tile changes anything is at the fixed point.
+// What bounds it is the longest least path: its iterations (about 110 VALU instructions, 0.2 us with a
+// wavefront per SIMD) and its tile crossings (an exchange, about 2 us).  1242x375: 228 -> 128 us for the
+// launch that works and the one that confirms; 2048x1024 (1,088 tiles): 624 -> 324 us of relaxation
+// over 32 launches, 160 of them in the working one.  The form before kept 32x64 tiles in LDS, four pixels a lane, at about 28
+// instructions and 5 LDS accesses a pixel and iteration, one column or row per iteration.
+// The launch counts the tiles that changed anything and those that left before they saw the whole
+// grid settled.  prev (nullable) is the counters of the launch before: when either of its counts is
+// zero the distances are already at the fixed point and the launch returns at once, with nothing
+// changed (so a fixed number of launches can be enqueued without reading anything back).  Each launch
+// clears the counters of the launch after the next, `next`, which nobody reads or writes meanwhile.
+// Without `wait` a workgroup takes several tiles in turn when the grid is smaller than their number.
+template <bool FAST>
+__global__ __launch_bounds__(kRelaxThreads, 5) void k_epic_relax(int W, int H, int kappa, uint64_t *keys,
+                                                                 const uint16_t *E, RelaxCounters now, int wait,
+                                                                 RelaxCounters prev, RelaxCounters next, int tiles_x,
+                                                                 int tiles)
+{
+    constexpr uint32_t wall = kWall<FAST>;
+    constexpr int R = kRRows;
+    uint32_t *const mail = now.mail, *const state = now.state;
+    if (threadIdx.x == 0) {
+        for (int t = (int)blockIdx.x; t < tiles; t += (int)gridDim.x) next.mail[t] = next.state[t] = 0u;
+        if (blockIdx.x == 0) *next.changed = *next.open = *next.done = 0u;
+    }
+    // (the same values in every block: an earlier kernel wrote them)
+    if (prev.changed && (*prev.changed == 0u || *prev.open == 0u)) return;
+    // row 0: the row above the tile; 1 + 2w, 2 + 2w: first and last row of wavefront w; then the row below
+    __shared__ uint64_t rows[2 * kRWaves + 2][64];
+    __shared__ uint32_t flags[2][kRWaves];
+    __shared__ uint32_t sides, poll;
+    for (int me = (int)blockIdx.x; me < tiles; me += (int)gridDim.x) {
+    const int tile_y = me / tiles_x, tile_x = me - tile_y * tiles_x;
+    const int nbr_tile[4] = {tile_x > 0 ? me - 1 : -1, tile_x + 1 < tiles_x ? me + 1 : -1,
+                             tile_y > 0 ? me - tiles_x : -1, me + tiles_x < tiles ? me + tiles_x : -1};
+    if (wait && threadIdx.x == 0) store_word(state + me, 2u);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int x = tile_x * kRTX - 1 + lane, y0 = tile_y * kRTY + wave * R;
+    const bool halo = lane == 0 || lane == 63, in_x = x >= 0 && x < W;
+    // the run's pixels that belong to the tile (bit j)
+    const uint32_t mine = in_x && !halo ? (1u << clampi(H - y0, 0, R)) - 1u : 0u;
+    auto at = [&](int y) { return (int64_t)y * W + x; };
+    auto load = [&](int y) { return in_x && y >= 0 && y < H ? key_of<FAST>(load_key(keys + at(y))) : key_of<FAST>(kNoKey); };
+    auto put_row = [&](int r, uint64_t k) {
+        __hip_atomic_store(&rows[r][lane], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto get_row = [&](int r) {
+        return __hip_atomic_load(&rows[r][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+
+    uint64_t own[R], snap[R]; // the pixels' keys, now and at the last check
+    uint32_t cl[R], cr[R];    // step costs from the left and the right neighbour
+    uint32_t cv[R + 1];       // between rows j - 1 and j (both ways)
+    {
+        uint32_t e[R + 2]; // edge values of rows -1 .. R
+#pragma unroll
+        for (int j = -1; j <= R; ++j) {
+            const int y = y0 + j;
+            e[j + 1] = in_x && y >= 0 && y < H ? E[at(y)] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            own[j] = load(y0 + j);
+            snap[j] = own[j];
+            const uint32_t ke = (uint32_t)kappa + e[j + 1];
+            const uint32_t l = ke + dppu<0x138>(e[j + 1]), r = ke + dppu<0x130>(e[j + 1]);
+            const bool in = (mine >> j) & 1u; // (pixels outside the image stay without a key)
+            cl[j] = in && x > 0 ? l : wall;
+            cr[j] = in && x + 1 < W ? r : wall;
+        }
+#pragma unroll
+        for (int j = 0; j <= R; ++j)
+            cv[j] = in_x && !halo && y0 + j > 0 && y0 + j < H ? (uint32_t)kappa + e[j] + e[j + 1] : wall;
+    }
+    put_row(1 + 2 * wave, own[0]);
+    put_row(2 + 2 * wave, own[R - 1]);
+    if (wave == 0) put_row(0, load(y0 - 1));
+    if (wave == kRWaves - 1) put_row(2 * kRWaves + 1, load(y0 + R));
     if (threadIdx.x == 0) sides = 0u;
     __syncthreads();
-    const int tx = threadIdx.x % kRTX, ty = threadIdx.x / kRTX;
-    constexpr int kPix = kRTX * kRTY / kRelaxThreads;
-    constexpr int kRowStep = kRelaxThreads / kRTX; // rows between a lane's pixels
-    int cell[kPix];
-    bool inside[kPix];
-    uint64_t own[kPix], orig[kPix], pub[kPix];
-    uint32_t cst[kPix][4]; // step costs from the left, right, upper and lower neighbour
-    uint32_t side_of[kPix]; // which neighbour tiles' halos this pixel belongs to (bit per side)
+
+    // re-read the neighbouring tiles' pixels
+    auto reload_halo = [&]() {
+        if (halo)
 #pragma unroll
-    for (int j = 0; j < kPix; ++j) {
-        const int lx = tx + 1, ly = ty + kRowStep * j + 1;
-        const int c = ly * kRTX2 + lx;
-        cell[j] = c;
-        inside[j] = x0 + lx < W && y0 + ly < H;
-        own[j] = orig[j] = pub[j] = K[0][c];
-        const uint32_t e = (uint32_t)kappa + Es[c];
-        cst[j][0] = e + Es[c - 1];
-        cst[j][1] = e + Es[c + 1];
-        cst[j][2] = e + Es[c - kRTX2];
-        cst[j][3] = e + Es[c + kRTX2];
-        side_of[j] = (lx == 1 ? 1u : 0u) | (lx == kRTX ? 2u : 0u) | (ly == 1 ? 4u : 0u) | (ly == kRTY ? 8u : 0u);
-    }
-    // re-read the halo ring into both buffers
-    auto reload_halo = [&](int cur) {
-        for (int i = threadIdx.x; i < 2 * kRTX2 + 2 * kRTY; i += kRelaxThreads) {
-            const int c = ring_cell(i);
-            uint32_t q;
-            if (!global_of(c, q)) continue;
-            const uint64_t k = load_key(keys + q);
-            if (k < K[cur][c]) {
-                K[0][c] = k;
-                K[1][c] = k;
+            for (int j = 0; j < R; ++j) {
+                own[j] = load(y0 + j);
+                snap[j] = own[j];
             }
-        }
+        if (wave == 0) put_row(0, load(y0 - 1));
+        if (wave == kRWaves - 1) put_row(2 * kRWaves + 1, load(y0 + R));
         __syncthreads();
     };
-    // publish newly improved border pixels and post mail to the tiles whose halos they touch
+    uint32_t pend = 0u, ever = 0u; // pixels changed since the last publication, and at all (bit j)
+    // the sides of the tile that pixel j lies on (bit per neighbour tile)
+    auto sides_of = [&](int j) {
+        return (lane == 1 ? 1u : 0u) | (lane == kRTX ? 2u : 0u) | (wave == 0 && j == 0 ? 4u : 0u) |
+               (wave == kRWaves - 1 && j == R - 1 ? 8u : 0u);
+    };
+    // publish changed border pixels and post mail to the tiles whose halos they touch
     auto publish = [&]() {
         uint32_t my_sides = 0u;
 #pragma unroll
-        for (int j = 0; j < kPix; ++j) {
-            if (inside[j] && side_of[j] && own[j] < pub[j]) {
-                const int ly = ty + kRowStep * j + 1;
-                const uint32_t q = (uint32_t)(y0 + ly) * (uint32_t)W + (uint32_t)(x0 + tx + 1);
-                atomicMin((unsigned long long *)(keys + q), (unsigned long long)own[j]);
-                pub[j] = own[j];
-                my_sides |= side_of[j];
+        for (int j = 0; j < R; ++j) {
+            const uint32_t sd = sides_of(j);
+            if (((pend >> j) & 1u) && sd) {
+                store_key(keys + at(y0 + j), own[j]);
+                my_sides |= sd;
             }
         }
+        pend = 0u;
         if (my_sides) atomicOr(&sides, my_sides);
-        __builtin_amdgcn_s_waitcnt(0); // the key updates are performed before any mail is posted
+        if (__ballot(my_sides != 0u)) __builtin_amdgcn_s_waitcnt(0); // the keys are there before the mail
         __syncthreads();
         if (threadIdx.x < 4 && ((sides >> threadIdx.x) & 1u) && nbr_tile[threadIdx.x] >= 0)
-            if (atomicExch(mail + nbr_tile[threadIdx.x], 1u) == 0u) atomicAdd(busy, 1u);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
+            store_word(mail + nbr_tile[threadIdx.x], 1u);
         if (threadIdx.x == 0) sides = 0u;
     };
-    // take this tile's mail; a working tile already holds a busy count and returns the one the
-    // mail carried, a still tile takes it over
-    auto take_mail = [&](bool still_now) {
+    // take this tile's mail and re-read the halo
+    auto take_mail = [&]() {
         if (threadIdx.x == 0) {
-            uint32_t m = 0u;
-            if (__hip_atomic_load(mail + me, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) m = atomicExch(mail + me, 0u);
-            if (m && !still_now) atomicSub(busy, 1u);
-            got_mail = m;
+            atomicExch(mail + me, 0u);
+            __builtin_amdgcn_s_waitcnt(0); // taken before the halo is read: later mail is kept
         }
         __syncthreads();
-        return got_mail != 0u;
+        reload_halo();
     };
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int cur = 0, polls = 0;
-    bool still = false;
-    for (int it = 0; it < kMaxIters; ++it) {
-        // all sixteen neighbour keys first (independent LDS reads, one wait), then the minima
-        const uint64_t *Kc = K[cur];
-        uint64_t nk[kPix][4];
-#pragma unroll
-        for (int j = 0; j < kPix; ++j) {
-            const int c = cell[j];
-            nk[j][0] = Kc[c - 1];
-            nk[j][1] = Kc[c + 1];
-            nk[j][2] = Kc[c - kRTX2];
-            nk[j][3] = Kc[c + kRTX2];
+    // (tile 0, all threads) 0: some tile is working or may, 1: none can change anything any more, 2: some
+    // have not started
+    auto all_settled = [&]() {
+        uint32_t first = 0u, second = 0u, letters = 0u, still = 1u, started = 2u;
+        for (int i = (int)threadIdx.x; i < tiles; i += kRelaxThreads) {
+            const uint32_t v = load_word(state + i);
+            first += v; // (resume counts only grow, so sums will do)
+            still &= v;
+            started = v == 0u ? 0u : started;
         }
-        bool ch = false;
+        if (!__syncthreads_and(still & 1u)) return __syncthreads_and(started) ? 0 : 2;
+        for (int i = (int)threadIdx.x; i < tiles; i += kRelaxThreads) letters |= load_word(mail + i);
+        __builtin_amdgcn_s_waitcnt(0); // the mailboxes before the states
+        for (int i = (int)threadIdx.x; i < tiles; i += kRelaxThreads) {
+            const uint32_t v = load_word(state + i);
+            second += v;
+            still &= v;
+        }
+        return __syncthreads_and((still & 1u) && letters == 0u && first == second) ? 1 : 0;
+    };
+    int polls = 0;
+    uint32_t resumed = 0u;
+    bool settled = false; // left because no tile can change anything
+    for (int round = 0; round < kMaxRounds; ++round) {
+        const bool exchange = (round + 1) % kExchange == 0;
+        uint32_t mailed = 0u;
+        if (exchange && threadIdx.x == 0) mailed = load_word(mail + me); // in flight during the round
+        for (int it = 0; it < kInner; ++it) {
+            const uint64_t above = get_row(2 * wave), below = get_row(2 * wave + 3);
 #pragma unroll
-        for (int j = 0; j < kPix; ++j) {
-            uint64_t best = own[j];
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const uint64_t v = step_key(nk[j][d], cst[j][d]);
-                best = v < best ? v : best;
+            for (int j = 0; j < R; ++j) {
+                const uint64_t l = key_shift<0x138>(own[j]), r = key_shift<0x130>(own[j]);
+                own[j] = key_relax<FAST>(key_relax<FAST>(own[j], l, cl[j]), r, cr[j]);
             }
-            best = inside[j] ? best : own[j];
-            ch |= best < own[j];
-            own[j] = best;
-            K[cur ^ 1][cell[j]] = best;
-        }
-        // one barrier: each wavefront posts whether any of its lanes changed anything
-        const uint64_t changed_lanes = __ballot(ch);
-        if (lane == 0) flags[it & 1][wave] = changed_lanes != 0ull;
-        __syncthreads();
-        bool any = false;
+            own[0] = key_relax<FAST>(own[0], above, cv[0]);
 #pragma unroll
-        for (int w = 0; w < kRelaxThreads / 64; ++w) any |= flags[it & 1][w] != 0u;
-        cur ^= 1;
-        if (any && (it + 1) % kExchange != 0) continue;
+            for (int j = 1; j < R; ++j) own[j] = key_relax<FAST>(own[j], own[j - 1], cv[j]);
+            own[R - 1] = key_relax<FAST>(own[R - 1], below, cv[R]);
+#pragma unroll
+            for (int j = R - 2; j >= 0; --j) own[j] = key_relax<FAST>(own[j], own[j + 1], cv[j + 1]);
+            put_row(1 + 2 * wave, own[0]);
+            put_row(2 + 2 * wave, own[R - 1]);
+        }
+        uint32_t ch = 0u;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            ch |= (own[j] != snap[j] ? 1u : 0u) << j;
+            snap[j] = own[j];
+        }
+        ch &= mine;
+        pend |= ch;
+        ever |= ch;
+        // one barrier: each wavefront posts whether any of its lanes changed anything, the first also
+        // the mail.  (No change anywhere in a whole round: the rows read were the final ones, so this
+        // is the fixed point of the tile.)
+        const bool changed_lanes = __ballot(ch != 0u) != 0ull;
+        if (lane == 0) flags[round & 1][wave] = (changed_lanes ? 1u : 0u) | (mailed ? 2u : 0u);
+        __syncthreads();
+        uint32_t seen = 0u;
+#pragma unroll
+        for (int w = 0; w < kRWaves; ++w) seen |= flags[round & 1][w];
+        const bool any = (seen & 1u) != 0u;
+        if (any && !exchange) continue;
         publish();
-        if (take_mail(false)) {
-            reload_halo(cur);
+        if (seen & 2u) {
+            take_mail();
             continue;
         }
         if (any) continue;
         // still
-        if (threadIdx.x == 0) atomicSub(busy, 1u);
-        still = true;
-        if (!wait) break;
+        if (wait && threadIdx.x == 0) {
+            __builtin_amdgcn_s_waitcnt(0); // the mail it posted is there
+            store_word(state + me, 4u * resumed + 3u);
+        }
         bool resume = false;
         while (polls < kMaxPolls) {
-            ++polls;
-            __builtin_amdgcn_s_sleep(2);
             if (threadIdx.x == 0)
-                count_zero = __hip_atomic_load(busy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+                poll = (load_word(mail + me) ? 1u : 0u) | (wait && me != 0 ? load_word(now.done) << 1 : 0u);
             __syncthreads();
-            const bool zero = count_zero != 0u;
-            if (take_mail(true)) {
-                resume = true;
-                break;
+            const uint32_t p = poll;
+            resume = (p & 1u) != 0u;
+            settled = p == 2u * kDone;
+            if (p || !wait) break;
+            ++polls;
+            if (me == 0) {
+                const int all = all_settled();
+                settled = all == 1;
+                const bool leave = settled || (all == 2 && polls >= kStartPolls);
+                if (leave && threadIdx.x == 0) store_word(now.done, settled ? kDone : kLeave);
+                if (leave) break;
             }
-            if (zero) break;
+            __builtin_amdgcn_s_sleep(kPollSleep);
+            __syncthreads();
         }
         if (!resume) break;
-        still = false;
-        reload_halo(cur);
-    }
-    // leave: return the busy count of a working tile and of any mail not taken
-    bool wrote = false;
-#pragma unroll
-    for (int j = 0; j < kPix; ++j) {
-        if (inside[j] && own[j] < orig[j]) {
-            const int ly = ty + kRowStep * j + 1;
-            const uint32_t q = (uint32_t)(y0 + ly) * (uint32_t)W + (uint32_t)(x0 + tx + 1);
-            atomicMin((unsigned long long *)(keys + q), (unsigned long long)own[j]);
-            wrote = true;
+        ++resumed;
+        if (wait && threadIdx.x == 0) {
+            store_word(state + me, 4u * resumed + 2u);
+            __builtin_amdgcn_s_waitcnt(0); // working again before the mail is taken
         }
+        take_mail();
     }
+    // leave
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+        if ((ever >> j) & 1u) store_key(keys + at(y0 + j), own[j]);
+    const bool wrote = __syncthreads_or(ever != 0u) != 0;
     if (threadIdx.x == 0) {
-        if (!still) atomicSub(busy, 1u);
-        if (atomicExch(mail + me, 0u)) atomicSub(busy, 1u);
+        if (!settled) atomicAdd(now.open, 1u);
+        if (wrote) atomicAdd(now.changed, 1u);
     }
-    if (__syncthreads_or(wrote) && threadIdx.x == 0) atomicAdd(changed, 1u);
-}
-
-// (one block) Keeps the changed count of the previous group's last launch (prev_last >= 0) in
-// carry, then clears the counters of the next m launches.
-__global__ void k_epic_clear_launch_counters(uint32_t *changed, uint32_t *busy, uint32_t *mail, int m,
-                                             uint32_t tiles, uint32_t *carry, int prev_last)
-{
-    if (prev_last >= 0 && threadIdx.x == 0) *carry = changed[prev_last];
-    __syncthreads();
-    if ((int)threadIdx.x < m) {
-        changed[threadIdx.x] = 0u;
-        busy[threadIdx.x] = tiles;
-    }
-    for (int64_t i = threadIdx.x; i < (int64_t)m * tiles; i += blockDim.x) mail[i] = 0u;
+    } // tiles
 }
 
 // Insert (or lower) the edge s -> t of length w into s's adjacency row: a slot holds
@@ -916,9 +1022,11 @@ int epic_run(const dgf_image *I0, const float *points, const float *flow, const 
     hipStream_t st = (hipStream_t)stream;
     const int64_t N = (int64_t)W * H;
 
+    const dim3 tiles((unsigned)((W + kRTX - 1) / kRTX), (unsigned)((H + kRTY - 1) / kRTY));
+    const int64_t ntiles = (int64_t)tiles.x * tiles.y;
     const int64_t prep_items = N > n * kMaxDeg ? N : n * kMaxDeg;
     hipLaunchKernelGGL(k_epic_prep, dim3(grid_for(prep_items, 256)), dim3(256), 0, st, (const uint8_t *)I0->data,
-                       I0->pitch_bytes, W, H, n, ws);
+                       I0->pitch_bytes, W, H, n, (uint32_t)ntiles, ws);
     if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
     uint32_t *err = ws.ctr + kChunk;
     const uint32_t *unsettled = nullptr; // (the async form) the last relaxation launch's changed count
@@ -926,44 +1034,49 @@ int epic_run(const dgf_image *I0, const float *points, const float *flow, const 
         hipLaunchKernelGGL(k_epic_seed, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, points, flow, status, n, W,
                            H, ws.keys);
         if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
-        const dim3 tiles((unsigned)((W + kRTX - 1) / kRTX), (unsigned)((H + kRTY - 1) / kRTY));
-        const int64_t ntiles = (int64_t)tiles.x * tiles.y;
         // tiles may wait for each other only if the whole grid is resident at once
+        const bool fast = (uint64_t)(W - 1 + H - 1) * (uint64_t)(o.kappa + 2 * kMaxEdge) < kFar &&
+                          o.kappa + 2 * kMaxEdge < (int)kFar;
+        const void *kernel = fast ? (const void *)k_epic_relax<true> : (const void *)k_epic_relax<false>;
         int dev = 0, cus = 0, per_cu = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_epic_relax, kRelaxThreads, 0) != hipSuccess)
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kRelaxThreads, 0) != hipSuccess)
             return DGF_ERR_HIP;
         const int wait = ntiles <= (int64_t)cus * per_cu ? 1 : 0;
-        uint32_t *busy = ws.ctr + kChunk + 2, *carry = ws.ctr + 2 * kChunk + 2;
         const bool sync = max_relax == 0;
         const int limit = sync ? kMaxRelaxLaunches : max_relax;
+        // a grid that fits the chip settles in its first launch, unless other work keeps it from
+        // being resident, and the second says so; the launches after that mostly return at once, and
+        // a few workgroups do so sooner than one for each tile (2.5 against 5 us on 1,088 tiles)
+        auto blocks = [&](int launch) {
+            return dim3((unsigned)(wait && launch >= 2 ? std::min<int64_t>(ntiles, kRestBlocks) : ntiles));
+        };
         bool converged = false;
-        int last = 0; // the index of the last launch of the last group
+        int done = 0; // launches so far; launch j uses counter set j mod kChunk
         // when the tiles can wait for each other one launch usually reaches the fixed point, so
         // the first check comes after two launches (work + confirmation), later ones after kChunk;
         // a launch after one that changed nothing returns at once
-        for (int base = 0, chunk = wait ? 2 : kChunk; base < limit && !converged; base += chunk, chunk = kChunk) {
-            chunk = chunk < limit - base ? chunk : limit - base;
-            hipLaunchKernelGGL(k_epic_clear_launch_counters, dim3(1), dim3(256), 0, st, ws.ctr, busy, ws.mail,
-                               chunk, (uint32_t)ntiles, carry, base > 0 ? last : -1);
-            for (int j = 0; j < chunk; ++j)
-                hipLaunchKernelGGL(k_epic_relax, tiles, dim3(kRelaxThreads), 0, st, W, H, o.kappa, ws.keys,
-                                   (const uint16_t *)ws.E, ws.ctr + j, busy + j, ws.mail + j * ntiles, wait,
-                                   j > 0 ? (const uint32_t *)(ws.ctr + j - 1) : (base > 0 ? (const uint32_t *)carry : nullptr));
-            if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
-            last = chunk - 1;
+        for (int chunk = wait ? 2 : kChunk; done < limit && !converged; chunk = kChunk) {
+            for (int end = done + (chunk < limit - done ? chunk : limit - done); done < end; ++done) {
+                const RelaxCounters prev = done > 0 ? relax_counters(ws, done - 1, ntiles) : RelaxCounters{};
+                hipLaunchKernelGGL(fast ? k_epic_relax<true> : k_epic_relax<false>, blocks(done), dim3(kRelaxThreads), 0, st,
+                                   W, H, o.kappa, ws.keys, (const uint16_t *)ws.E, relax_counters(ws, done, ntiles),
+                                   wait && done < 2 ? 1 : 0, prev, relax_counters(ws, done + 2, ntiles), (int)tiles.x,
+                                   (int)ntiles);
+                if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
+            }
             if (sync) {
-                uint32_t h_changed[kChunk];
-                if (hipMemcpyAsync(h_changed, ws.ctr, sizeof(uint32_t) * chunk, hipMemcpyDeviceToHost, st) !=
-                        hipSuccess ||
+                uint32_t h_changed = 0;
+                if (hipMemcpyAsync(&h_changed, ws.ctr + (done - 1) % kChunk, sizeof(uint32_t), hipMemcpyDeviceToHost,
+                                   st) != hipSuccess ||
                     hipStreamSynchronize(st) != hipSuccess)
                     return DGF_ERR_HIP;
-                converged = h_changed[chunk - 1] == 0u;
+                converged = h_changed == 0u;
             }
         }
         if (sync && !converged) return DGF_ERR_UNSUPPORTED;
-        unsettled = sync ? nullptr : ws.ctr + last;
+        unsettled = sync ? nullptr : ws.ctr + (done - 1) % kChunk;
         hipLaunchKernelGGL(k_epic_graph, dim3(grid_for(N, 256)), dim3(256), 0, st, W, H, o.kappa,
                            (const uint64_t *)ws.keys, (const uint16_t *)ws.E, ws, err, unsettled);
         if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
