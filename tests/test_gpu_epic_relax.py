@@ -38,3 +38,24 @@ def test_cells_and_distances(W, H, n, kappa, run):
     _, o = oracle.epic(I0, P.astype(np.float64), F.astype(np.float64), st, k=4, kappa=kappa, h=64, full=True)
     assert np.array_equal(g["labels"], o["L"])
     assert np.array_equal(g["dist"].view(np.uint32).astype(np.int64), np.where(o["D"] < 0, 0xFFFFFFFF, o["D"]))
+
+
+@pytest.mark.parametrize("W,H,step", [(64, 32, 1), (65, 33, 1), (130, 70, 1), (131, 67, 2), (63, 100, 3)])
+def test_graph_of_dense_seeds(W, H, step):
+    """A seed on every pixel (every second, every third): more touching cells in a 64 x 32 graph tile
+    than its table of 1,024 holds, so part of them goes to the rows directly; neighbour lists and
+    graph distances bit for bit."""
+    rng = np.random.default_rng(W + H + step)
+    I0 = rng.integers(0, 256, (H, W)).astype(np.uint8)
+    y, x = np.mgrid[0:H:step, 0:W:step]
+    P = np.stack([x.ravel(), y.ravel()], 1).astype(np.float32)
+    F = rng.normal(size=P.shape).astype(np.float32)
+    st = np.zeros(len(P), np.uint8)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    _, aux = dgf.epic(t(I0), t(P), t(F), t(st), opts=dgf.EpicOpts(k=16), return_aux=True)
+    torch.cuda.synchronize()
+    g = {k: v.cpu().numpy() for k, v in aux.items()}
+    _, o = oracle.epic(I0, P.astype(np.float64), F.astype(np.float64), st, k=16, full=True)
+    assert np.array_equal(g["labels"], o["L"])
+    assert np.array_equal(g["nbr"], o["nb"])
+    assert np.array_equal(g["nbr_dist"].view(np.uint32).astype(np.int64), np.where(o["nd"] < 0, 0xFFFFFFFF, o["nd"]))
