@@ -1092,6 +1092,50 @@ int epic_run(const dgf_image *I0, const float *points, const float *flow, const 
                        I0->pitch_bytes, W, H, n, (uint32_t)ntiles, ws);
     if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
     uint32_t *err = ws.ctr + kChunk;
+    // everything after the partition; unsettled (nullable): nothing is done when this word is not zero
+    auto finish = [&](const uint32_t *unsettled) {
+        if (n > 0) {
+            const int gh = kGraphWaves * kGraphRows;
+            hipLaunchKernelGGL(k_epic_graph, dim3((unsigned)((W + kGraphW - 1) / kGraphW), (unsigned)((H + gh - 1) / gh)),
+                               dim3(64 * kGraphWaves), 0, st, W, H, o.kappa, (const uint64_t *)ws.keys,
+                               (const uint16_t *)ws.E, ws, err, unsettled);
+            if (hipGetLastError() != hipSuccess) return false;
+            hipLaunchKernelGGL(k_epic_least, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, n, ws, unsettled);
+            if (hipGetLastError() != hipSuccess) return false;
+            EpicFit F{};
+            F.pts = points;
+            F.flow = flow;
+            F.status = status;
+            F.keys = ws.keys;
+            F.ws = ws;
+            F.n = n;
+            F.W = W;
+            F.H = H;
+            F.k = o.k;
+            F.h = o.half_dist;
+            F.dmax = (uint32_t)(64u * (uint32_t)o.half_dist);
+            F.nbr = nbr;
+            F.nbr_dist = nbr_dist;
+            F.model_out = model;
+            F.err = err;
+            F.unsettled = unsettled;
+            if (o.k <= 128)
+                hipLaunchKernelGGL(k_epic_knn_fit<2>, dim3((unsigned)n), dim3(64), 0, st, F);
+            else
+                hipLaunchKernelGGL(k_epic_knn_fit<kMaxK / 64>, dim3((unsigned)n), dim3(64), 0, st, F);
+            if (hipGetLastError() != hipSuccess) return false;
+        }
+        hipLaunchKernelGGL(k_epic_dense, dim3(grid_for(N, 256)), dim3(256), 0, st, W, H, (const uint64_t *)ws.keys,
+                           (const float *)ws.model, points, dense, dense_pitch, labels, dist, unsettled);
+        return hipGetLastError() == hipSuccess;
+    };
+    // (synchronises) the counters: h[launch mod kChunk] tiles changed, h[kChunk] errors, then the open counts
+    uint32_t h[2 * kChunk + 1] = {};
+    auto counters = [&]() {
+        return hipMemcpyAsync(h, ws.ctr, sizeof(h), hipMemcpyDeviceToHost, st) == hipSuccess &&
+               hipStreamSynchronize(st) == hipSuccess;
+    };
+    const bool sync = max_relax == 0;
     const uint32_t *unsettled = nullptr; // (the async form) the last relaxation launch's changed count
     if (n > 0) {
         hipLaunchKernelGGL(k_epic_seed, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, points, flow, status, n, W,
@@ -1107,7 +1151,6 @@ int epic_run(const dgf_image *I0, const float *points, const float *flow, const 
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kRelaxThreads, 0) != hipSuccess)
             return DGF_ERR_HIP;
         const int wait = ntiles <= (int64_t)cus * per_cu ? 1 : 0;
-        const bool sync = max_relax == 0;
         const int limit = sync ? kMaxRelaxLaunches : max_relax;
         // a grid that fits the chip settles in its first launch, unless other work keeps it from
         // being resident, and the second says so; the launches after that mostly return at once, and
@@ -1115,73 +1158,44 @@ int epic_run(const dgf_image *I0, const float *points, const float *flow, const 
         auto blocks = [&](int launch) {
             return dim3((unsigned)(wait && launch >= 2 ? std::min<int64_t>(ntiles, kRestBlocks) : ntiles));
         };
-        bool converged = false;
         int done = 0; // launches so far; launch j uses counter set j mod kChunk
-        // when the tiles can wait for each other one launch usually reaches the fixed point, so
-        // the first check comes after two launches (work + confirmation), later ones after kChunk;
-        // a launch after one that changed nothing returns at once
-        for (int chunk = wait ? 2 : kChunk; done < limit && !converged; chunk = kChunk) {
-            for (int end = done + (chunk < limit - done ? chunk : limit - done); done < end; ++done) {
+        auto relax = [&](int launches) {
+            for (const int end = done + std::min(launches, limit - done); done < end; ++done) {
                 const RelaxCounters prev = done > 0 ? relax_counters(ws, done - 1, ntiles) : RelaxCounters{};
                 hipLaunchKernelGGL(fast ? k_epic_relax<true> : k_epic_relax<false>, blocks(done), dim3(kRelaxThreads), 0, st,
                                    W, H, o.kappa, ws.keys, (const uint16_t *)ws.E, relax_counters(ws, done, ntiles),
                                    wait && done < 2 ? 1 : 0, prev, relax_counters(ws, done + 2, ntiles), (int)tiles.x,
                                    (int)ntiles);
-                if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
+                if (hipGetLastError() != hipSuccess) return false;
             }
-            if (sync) {
-                uint32_t h_changed = 0;
-                if (hipMemcpyAsync(&h_changed, ws.ctr + (done - 1) % kChunk, sizeof(uint32_t), hipMemcpyDeviceToHost,
-                                   st) != hipSuccess ||
-                    hipStreamSynchronize(st) != hipSuccess)
-                    return DGF_ERR_HIP;
-                converged = h_changed == 0u;
-            }
+            return true;
+        };
+        if (sync && wait) {
+            // the launch that settles a resident grid, with all that follows behind it on the condition
+            // that it did: one round trip to the host in all
+            if (!relax(1) || !finish(relax_counters(ws, 0, ntiles).open) || !counters()) return DGF_ERR_HIP;
+            if (h[kChunk + 1] == 0u) return h[kChunk] ? DGF_ERR_CAPACITY : DGF_OK;
         }
-        if (sync && !converged) return DGF_ERR_UNSUPPORTED;
-        unsettled = sync ? nullptr : ws.ctr + (done - 1) % kChunk;
-        const int gh = kGraphWaves * kGraphRows;
-        hipLaunchKernelGGL(k_epic_graph, dim3((unsigned)((W + kGraphW - 1) / kGraphW), (unsigned)((H + gh - 1) / gh)),
-                           dim3(64 * kGraphWaves), 0, st, W, H, o.kappa, (const uint64_t *)ws.keys,
-                           (const uint16_t *)ws.E, ws, err, unsettled);
-        if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
-        hipLaunchKernelGGL(k_epic_least, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, n, ws, unsettled);
-        if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
-        EpicFit F{};
-        F.pts = points;
-        F.flow = flow;
-        F.status = status;
-        F.keys = ws.keys;
-        F.ws = ws;
-        F.n = n;
-        F.W = W;
-        F.H = H;
-        F.k = o.k;
-        F.h = o.half_dist;
-        F.dmax = (uint32_t)(64u * (uint32_t)o.half_dist);
-        F.nbr = nbr;
-        F.nbr_dist = nbr_dist;
-        F.model_out = model;
-        F.err = err;
-        F.unsettled = unsettled;
-        if (o.k <= 128)
-            hipLaunchKernelGGL(k_epic_knn_fit<2>, dim3((unsigned)n), dim3(64), 0, st, F);
-        else
-            hipLaunchKernelGGL(k_epic_knn_fit<kMaxK / 64>, dim3((unsigned)n), dim3(64), 0, st, F);
-        if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
+        if (sync) {
+            // checked every kChunk launches; a launch after one that changed nothing returns at once
+            bool converged = false;
+            while (done < limit && !converged) {
+                if (!relax(kChunk) || !counters()) return DGF_ERR_HIP;
+                converged = h[(done - 1) % kChunk] == 0u;
+            }
+            if (!converged) return DGF_ERR_UNSUPPORTED;
+        } else {
+            if (!relax(limit)) return DGF_ERR_HIP;
+            unsettled = ws.ctr + (done - 1) % kChunk;
+        }
     }
-    hipLaunchKernelGGL(k_epic_dense, dim3(grid_for(N, 256)), dim3(256), 0, st, W, H, (const uint64_t *)ws.keys,
-                       (const float *)ws.model, points, dense, dense_pitch, labels, dist, unsettled);
-    if (hipGetLastError() != hipSuccess) return DGF_ERR_HIP;
-    if (max_relax > 0) {
+    if (!finish(unsettled)) return DGF_ERR_HIP;
+    if (!sync) {
         hipLaunchKernelGGL(k_epic_status, dim3(1), dim3(1), 0, st, status_out, unsettled, (const uint32_t *)err);
         return hipGetLastError() == hipSuccess ? DGF_OK : DGF_ERR_HIP;
     }
-    uint32_t h_err = 0;
-    if (hipMemcpyAsync(&h_err, err, sizeof(h_err), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return DGF_ERR_HIP;
-    return h_err ? DGF_ERR_CAPACITY : DGF_OK;
+    if (!counters()) return DGF_ERR_HIP;
+    return h[kChunk] ? DGF_ERR_CAPACITY : DGF_OK;
 }
 
 } // namespace
