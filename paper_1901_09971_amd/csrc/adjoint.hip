@@ -59,19 +59,6 @@ __device__ __forceinline__ void psi_and_slope(const AdjParams &A, float r, float
     }
 }
 
-__device__ __forceinline__ int adj_pair_of(const AdjParams &A, int64_t i)
-{
-    int lo = 0, hi = A.npairs - 1; // last pair whose first point is <= i
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (A.pt_off[mid] <= i)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
-}
-
 template <typename PixT>
 __global__ __launch_bounds__(64) void k_track_adjoint(AdjParams A)
 {
@@ -498,7 +485,7 @@ hipError_t launch_track_adjoint(const AdjParams &A0, int dtype, hipStream_t st)
     if (A0.n <= 0) return hipSuccess;
     AdjParams A = A0;
     A.perm_mul = scatter_multiplier(A.n);
-    if (dtype == DGF_F32 && !A.npairs && adjoint_support_compiled(A.s)) return launch_adjoint_direct(A, st);
+    if (adjoint_support_compiled(A.s) && (dtype == DGF_U8) == (A.npairs > 0)) return launch_adjoint_direct(A, st);
     const size_t lds = adjoint_lds_bytes(A.s);
     if (A.illum) {
         if (dtype == DGF_U8)

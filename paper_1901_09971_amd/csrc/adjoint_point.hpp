@@ -6,6 +6,20 @@
 
 namespace dgf {
 
+// The pair of a batch plan that point i belongs to.
+__device__ __forceinline__ int adj_pair_of(const AdjParams &A, int64_t i)
+{
+    int lo = 0, hi = A.npairs - 1; // last pair whose first point is <= i
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (A.pt_off[mid] <= i)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
+}
+
 // ---- the adjoint of one point for a support size fixed at compile time ------------------------
 //
 // The same quantities by the same formulas as k_track_adjoint and k_track_adjoint_illum, split so

@@ -145,15 +145,19 @@ hipError_t launch_tiled(const AdjParams &A, unsigned tiles, size_t lds, hipStrea
 
 } // namespace
 
-// Tile shape for a pair of nx x ny grid points: the largest of a few shapes whose two LDS tiles let
-// two workgroups share a CU.  The dI0 tile holds the patches of a full tile of windows wherever the
+// Tile shape for a pair of nx x ny grid points of a plan of n points: the largest of a few shapes whose
+// two LDS tiles let two workgroups share a CU and that leaves the chip at least kMinTiles workgroups
+// (a wavefront takes its points one after the other, so a small plan needs more workgroups more than
+// it needs fewer atomics).  The dI0 tile holds the patches of a full tile of windows wherever the
 // centroids fall in them; the dI1 tile leaves room for a quarter more spread and 8 px of it.
-void adjoint_tile_shape(AdjPair &P, int nx, int ny, int s, int win, int stride)
+void adjoint_tile_shape(AdjPair &P, int nx, int ny, int s, int win, int stride, int64_t n)
 {
+    constexpr int64_t kMinTiles = 1024;
     const size_t budget = 78 * 1024 - kAdjWaves * wave_bytes(s);
     const int W0 = s + 3, W1 = s + 1;
     static const int shapes[][2] = {{16, 8}, {8, 8}, {8, 4}, {4, 4}};
     for (const auto &sh : shapes) {
+        if (n < kMinTiles * sh[0] * sh[1]) continue;
         const int64_t ex = (int64_t)(sh[0] - 1) * stride, ey = (int64_t)(sh[1] - 1) * stride;
         const int64_t w0 = W0 + ex + win - 1, h0 = W0 + ey + win - 1;
         const int64_t w1 = W1 + ex + ex / 4 + win + 7, h1 = W1 + ey + ey / 4 + win + 7;
@@ -170,9 +174,9 @@ void adjoint_tile_shape(AdjPair &P, int nx, int ny, int s, int win, int stride)
         P.h1 = (int)h1;
         return;
     }
-    P.nx = nx * ny; // runs of points, no tiles
+    P.nx = nx * ny; // a point per wavefront, no tiles (in a plan that has tiles elsewhere)
     P.ny = 1;
-    P.tx = kAdjPoints;
+    P.tx = kAdjWaves;
     P.ty = 1;
     P.w0 = P.h0 = P.w1 = P.h1 = 0;
 }

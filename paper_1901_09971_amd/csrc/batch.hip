@@ -342,7 +342,7 @@ int dgf_batch_create(const dgf_pair_desc *pairs, int32_t npairs, int32_t levels,
                          g0, g0 + wh, d.I0.width, d.I0.width, d.I0.width, d.I0.height, 0, 0, 0, 0, 0, 0, 0, 0, 0};
         b->grad_off[i + 1] = g0 + 2 * wh;
         if (!adjoint_support_compiled(support)) continue;
-        adjoint_tile_shape(adj[i], det[i].nx, det[i].ny, support, d.window, d.stride);
+        adjoint_tile_shape(adj[i], det[i].nx, det[i].ny, support, d.window, d.stride, b->total_pts);
         adj[i].tile_first = b->adj_tiles;
         b->adj_tiles += adjoint_tiles(adj[i]);
         b->adj_tile_floats = std::max(b->adj_tile_floats, adjoint_tile_floats(adj[i]));
@@ -488,8 +488,8 @@ int dgf_batch_backward(dgf_batch *b, const float *points, const float *flow, con
     A.illum = im ? illum : nullptr;
     A.n = b->total_pts;
     fill_adjoint_constants(A, b->opts);
-    const hipError_t e = adjoint_support_compiled(b->s) ? launch_adjoint_tiled(A, b->adj_tiles, b->adj_tile_floats, st)
-                                                        : launch_track_adjoint(A, b->dtype, st);
+    const hipError_t e = b->adj_tile_floats > 0 ? launch_adjoint_tiled(A, b->adj_tiles, b->adj_tile_floats, st)
+                                                : launch_track_adjoint(A, b->dtype, st);
     return e == hipSuccess ? DGF_OK : DGF_ERR_HIP;
 }
 

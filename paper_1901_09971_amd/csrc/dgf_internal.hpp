@@ -781,7 +781,7 @@ hipError_t launch_detect_backward(const DetectGradParams &G, hipStream_t st);
 hipError_t launch_track_adjoint(const AdjParams &A, int dtype, hipStream_t st);
 bool adjoint_support_compiled(int s); // a fixed-size adjoint exists for this support
 hipError_t launch_adjoint_direct(const AdjParams &A, hipStream_t st);
-void adjoint_tile_shape(AdjPair &P, int nx, int ny, int s, int win, int stride);
+void adjoint_tile_shape(AdjPair &P, int nx, int ny, int s, int win, int stride, int64_t n);
 size_t adjoint_tile_floats(const AdjPair &P);
 int64_t adjoint_tiles(const AdjPair &P);
 hipError_t launch_adjoint_tiled(const AdjParams &A, int64_t tiles, size_t tile_floats, hipStream_t st);
