@@ -111,27 +111,12 @@ int dgf_pyramid(const dgf_image *src, int32_t levels, void *dst, size_t dst_byte
     const size_t need = dgf_pyramid_layout(src->width, src->height, levels, src->dtype, off, pitch);
     if (levels == 1) return DGF_OK;
     if (!dst || dst_bytes < need) return DGF_ERR_WORKSPACE;
-    const uint8_t *prev = (const uint8_t *)src->data;
-    int64_t prev_pitch = src->pitch_bytes;
-    int W = src->width, H = src->height;
-    if (src->dtype == DGF_U8) {
-        const uint8_t *srcs[2] = {prev, nullptr};
-        const int64_t sp[2] = {prev_pitch, 0};
-        uint8_t *lvl[2][DGF_MAX_LEVELS] = {};
-        for (int l = 1; l < levels; ++l) lvl[0][l] = (uint8_t *)dst + off[l];
-        return launch_pyr_chains(srcs, sp, lvl, pitch, W, H, levels, 1, (hipStream_t)stream) == hipSuccess ? DGF_OK
-                                                                                                          : DGF_ERR_HIP;
-    }
-    for (int l = 1; l < levels; ++l) {
-        PyrJob j{prev, (uint8_t *)dst + off[l], prev_pitch, pitch[l], W, H};
-        const hipError_t e = launch_pyr_level(&j, 1, src->dtype, (hipStream_t)stream);
-        if (e != hipSuccess) return DGF_ERR_HIP;
-        prev = (const uint8_t *)dst + off[l];
-        prev_pitch = pitch[l];
-        W = (W + 1) / 2;
-        H = (H + 1) / 2;
-    }
-    return DGF_OK;
+    const uint8_t *srcs[2] = {(const uint8_t *)src->data, nullptr};
+    const int64_t sp[2] = {src->pitch_bytes, 0};
+    uint8_t *lvl[2][DGF_MAX_LEVELS] = {};
+    for (int l = 1; l < levels; ++l) lvl[0][l] = (uint8_t *)dst + off[l];
+    return hip_rc(launch_pyr_chains(srcs, sp, lvl, pitch, src->width, src->height, levels, 1, src->dtype,
+                                    (hipStream_t)stream));
 }
 
 size_t dgf_track_workspace_bytes(int32_t W, int32_t H, int32_t levels, int32_t dtype)
@@ -152,8 +137,7 @@ int check_pair(const dgf_image *I0, const dgf_image *I1, int32_t levels)
 }
 
 // Level descriptors of both pyramids inside a track workspace (level 0 = the inputs).
-void pyramid_levels(const dgf_image *I0, const dgf_image *I1, int32_t levels, const void *workspace, LevelPair *lv,
-                    PyrJob *jobs /* nullable, [levels][2] */)
+void pyramid_levels(const dgf_image *I0, const dgf_image *I1, int32_t levels, const void *workspace, LevelPair *lv)
 {
     int64_t off[DGF_MAX_LEVELS], pitch[DGF_MAX_LEVELS];
     const size_t pyr_bytes = dgf_pyramid_layout(I0->width, I0->height, levels, I0->dtype, off, pitch);
@@ -163,10 +147,6 @@ void pyramid_levels(const dgf_image *I0, const dgf_image *I1, int32_t levels, co
                       I0->height};
     int W = I0->width, H = I0->height;
     for (int l = 1; l < levels; ++l) {
-        if (jobs) {
-            jobs[2 * l] = PyrJob{lv[l - 1].p0, ws0 + off[l], lv[l - 1].pitch0, pitch[l], W, H};
-            jobs[2 * l + 1] = PyrJob{lv[l - 1].p1, ws1 + off[l], lv[l - 1].pitch1, pitch[l], W, H};
-        }
         W = (W + 1) / 2;
         H = (H + 1) / 2;
         lv[l] = LevelPair{ws0 + off[l], ws1 + off[l], pitch[l], pitch[l], W, H};
@@ -184,28 +164,18 @@ int dgf_track_pyramids(const dgf_image *I0, const dgf_image *I1, int32_t levels,
     if (!workspace || ws_bytes < dgf_track_workspace_bytes(I0->width, I0->height, levels, I0->dtype))
         return DGF_ERR_WORKSPACE;
     LevelPair lv[DGF_MAX_LEVELS];
-    PyrJob jobs[2 * DGF_MAX_LEVELS];
-    pyramid_levels(I0, I1, levels, workspace, lv, jobs);
-    if (I0->dtype == DGF_U8) {
-        const uint8_t *srcs[2] = {lv[0].p0, lv[0].p1};
-        const int64_t sp[2] = {lv[0].pitch0, lv[0].pitch1};
-        uint8_t *lvl[2][DGF_MAX_LEVELS] = {};
-        int64_t pitch[DGF_MAX_LEVELS] = {};
-        for (int l = 1; l < levels; ++l) {
-            lvl[0][l] = (uint8_t *)lv[l].p0;
-            lvl[1][l] = (uint8_t *)lv[l].p1;
-            pitch[l] = lv[l].pitch0;
-        }
-        return launch_pyr_chains(srcs, sp, lvl, pitch, I0->width, I0->height, levels, 2, (hipStream_t)stream) ==
-                       hipSuccess
-                   ? DGF_OK
-                   : DGF_ERR_HIP;
-    }
+    pyramid_levels(I0, I1, levels, workspace, lv);
+    const uint8_t *srcs[2] = {lv[0].p0, lv[0].p1};
+    const int64_t sp[2] = {lv[0].pitch0, lv[0].pitch1};
+    uint8_t *lvl[2][DGF_MAX_LEVELS] = {};
+    int64_t pitch[DGF_MAX_LEVELS] = {};
     for (int l = 1; l < levels; ++l) {
-        const hipError_t e = launch_pyr_level(&jobs[2 * l], 2, I0->dtype, (hipStream_t)stream);
-        if (e != hipSuccess) return DGF_ERR_HIP;
+        lvl[0][l] = (uint8_t *)lv[l].p0;
+        lvl[1][l] = (uint8_t *)lv[l].p1;
+        pitch[l] = lv[l].pitch0;
     }
-    return DGF_OK;
+    return hip_rc(launch_pyr_chains(srcs, sp, lvl, pitch, I0->width, I0->height, levels, 2, I0->dtype,
+                                    (hipStream_t)stream));
 }
 
 int dgf_detect_pyramids(const dgf_image *I0, const dgf_image *I1, int32_t window, int32_t stride, int32_t levels,
@@ -231,7 +201,7 @@ int dgf_detect_pyramids(const dgf_image *I0, const dgf_image *I1, int32_t window
         return dgf_track_pyramids(I0, I1, levels, workspace, ws_bytes, stream);
     }
     LevelPair lv[DGF_MAX_LEVELS];
-    pyramid_levels(I0, I1, levels, workspace, lv, nullptr);
+    pyramid_levels(I0, I1, levels, workspace, lv);
     const uint8_t *srcs[2] = {lv[0].p0, lv[0].p1};
     const int64_t sp[2] = {lv[0].pitch0, lv[0].pitch1};
     uint8_t *lvl[2][DGF_MAX_LEVELS] = {};
@@ -253,7 +223,7 @@ int dgf_detect_pyramids(const dgf_image *I0, const dgf_image *I1, int32_t window
     D.tiles_x = (D.nx + 15) / 16;
     D.tiles_y = (D.ny + 15) / 16;
     D.o = DetectOut{points, sel, response};
-    return hip_rc(launch_pyr_chains(srcs, sp, lvl, pitch, I0->width, I0->height, levels, 2, st, &D));
+    return hip_rc(launch_pyr_chains(srcs, sp, lvl, pitch, I0->width, I0->height, levels, 2, DGF_U8, st, &D));
 }
 
 } // extern "C"
@@ -336,7 +306,7 @@ int track_run_with(const dgf_image *I0, const dgf_image *I1, const float *points
     if (track_lds_bytes(support, tune) > kMaxLdsPerBlock) return DGF_ERR_UNSUPPORTED;
     if (n == 0) return DGF_OK;
     TrackParams P{};
-    pyramid_levels(I0, I1, levels, workspace, P.lv, nullptr);
+    pyramid_levels(I0, I1, levels, workspace, P.lv);
     P.pts = points;
     P.n = n;
     P.flow = flow;

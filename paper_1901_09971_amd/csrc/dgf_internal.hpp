@@ -378,6 +378,53 @@ __device__ __forceinline__ bool stage_u8_w64(float *lds, int lp, const uint8_t *
     return true;
 }
 
+// stage_rect's interior case for float images: eight lanes per row, four texels per lane by one
+// 16-byte load (rows need only be 4-byte aligned), B steps of LPP / 8 rows in flight.  Qualifies when
+// cols <= 32 and every group of four lies inside the image; returns false, staging nothing,
+// otherwise.  When the row's last group fits the LDS row pitch it writes all four words into the
+// padding, which no reader looks at.  (One texel per lane and two rows in flight made a 20-row tile ten
+// round trips to L2: the tracker took 109 us on a 640x480 float pair at support 15, 99 now.)
+template <int LPP, int B>
+__device__ __forceinline__ bool stage_f32(float *lds, int lp, const uint8_t *base, int64_t pitch, int W, int H, int ox,
+                                          int oy, int rows, int cols, int li)
+{
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef const __attribute__((address_space(1))) uint8_t gbyte;
+    const int n4 = (cols + 3) >> 2;
+    if (!(cols <= 32 && ox >= 0 && oy >= 0 && ox + 4 * n4 <= W && oy + rows <= H)) return false;
+    constexpr int step = LPP / 8;
+    const int r0 = li >> 3, c4 = (li & 7) << 2;
+    if (c4 >= cols) return true;
+    gbyte *gb = (gbyte *)base;
+    const uint32_t pb = (uint32_t)pitch;
+    const uint32_t o0 = __umul24((uint32_t)(oy + r0), pb) + 4u * (uint32_t)(ox + c4);
+    const uint32_t last = __umul24((uint32_t)(oy + rows - 1), pb) + 4u * (uint32_t)(ox + c4);
+    const bool whole = 4 * n4 <= lp || c4 + 4 <= cols;
+    for (int k0 = 0; k0 * step < rows; k0 += B) {
+        f4 v[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) // a step past the last row loads that row again and writes nothing
+            v[k] = *(const __attribute__((address_space(1))) f4 *)(gb + min(o0 + (uint32_t)((k0 + k) * step) * pb, last));
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const int y = r0 + (k0 + k) * step;
+            if (y < rows) {
+                float *d = lds + y * lp + c4;
+                d[0] = v[k][0];
+                if (whole) {
+                    d[1] = v[k][1];
+                    d[2] = v[k][2];
+                    d[3] = v[k][3];
+                } else {
+                    if (c4 + 1 < cols) d[1] = v[k][1];
+                    if (c4 + 2 < cols) d[2] = v[k][2];
+                }
+            }
+        }
+    }
+    return true;
+}
+
 // A square rectangle (rows = cols) of at most 8 NS rows into LDS (B steps' loads in flight;
 // CROWS: its row count when fixed at compile time): the unrolled whole-wavefront form for uint8
 // images where it qualifies, stage_rect otherwise, its lane layout worked out there and then
@@ -388,6 +435,8 @@ __device__ __forceinline__ void stage_tile(float *lds, int lp, const uint8_t *ba
 {
     if constexpr (LPP == 64 && sizeof(PixT) == 1)
         if (stage_u8_w64<NS, B, CROWS>(lds, lp, base, pitch, W, H, ox, oy, rows, cols, li)) return;
+    if constexpr (sizeof(PixT) == 4)
+        if (stage_f32<LPP, LPP == 64 ? B : 5>(lds, lp, base, pitch, W, H, ox, oy, rows, cols, li)) return;
     stage_rect<LPP, PixT>(lds, lp, base, pitch, W, H, ox, oy, rows, cols, stage_lanes<LPP>(cols, li));
 }
 
@@ -848,9 +897,8 @@ struct DetectJob {
 size_t detect_tile_lds(int win, int stride);
 hipError_t launch_detect(const uint8_t *img, int64_t pitch, int W, int H, int win, int stride, float *pts,
                          uint8_t *sel, float *resp, hipStream_t st);
-hipError_t launch_pyr_level(const PyrJob *jobs, int njobs, int dtype, hipStream_t st);
 
-// Up to four consecutive uint8 levels of one or two images in one launch: level k (k = 1 .. m)
+// Up to four consecutive levels of one or two images in one launch: level k (k = 1 .. m)
 // of image f goes to dst[k - 1][f] with row pitch dst_pitch[k - 1]; W[0] x H[0] is the source
 // level, W[k] = ceil(W[k - 1] / 2).
 struct PyrChain {
@@ -887,7 +935,7 @@ bool front_detect_fits(int win, int stride);
 hipError_t launch_pyr_chain_u8(const PyrChain &A, int njobs, hipStream_t st, const FrontDetect *det = nullptr);
 hipError_t launch_pyr_chains(const uint8_t *const srcs[2], const int64_t src_pitch[2],
                              uint8_t *const lvl[2][DGF_MAX_LEVELS], const int64_t *pitch, int W, int H, int levels,
-                             int njobs, hipStream_t st, const FrontDetect *det = nullptr);
+                             int njobs, int dtype, hipStream_t st, const FrontDetect *det = nullptr);
 hipError_t launch_track(const TrackParams &P, const TrackTuning &T, int dtype, hipStream_t st);
 int pick_ppl_max(int s, int lpp);
 bool run_shape_compiled(int lpp, int s);
