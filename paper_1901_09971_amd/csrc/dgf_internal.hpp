@@ -861,11 +861,11 @@ struct GmFit {
     double *part;              // [2][npairs][nblk][kGmSums]
 };
 
-// Workgroups per pass for a pair of n points (about 2048 points each): a function of the pair's
+// Workgroups per pass for a pair of n points (about 512 points each, two per lane): a function of the pair's
 // own count, so that a pair fitted in a batch plan is reduced exactly as it is on its own.
 __host__ __device__ inline int gm_blocks(int64_t n)
 {
-    const int64_t b = (n + 2047) / 2048;
+    const int64_t b = (n + 511) / 512;
     return (int)(b < 1 ? 1 : (b > kGmMaxBlocks ? kGmMaxBlocks : b));
 }
 size_t gm_models_bytes(int npairs);

@@ -7,7 +7,17 @@
 // rebuilds the previous pass's model from the previous pass's partial sums (all workgroups of a pair
 // reduce the same partials in the same order, so they agree bit for bit), then sums its slice of the
 // pair's samples under the weights that model gives.  A last launch of one workgroup per pair turns
-// the final partial sums into the model.  Models and partials are double-buffered by pass parity, so
+// the final partial sums into the model.
+//
+// A launch is bound by its own latency -- launch, fetch, sum, solve, sum -- not by bytes or FP64
+// rate, so each part of that chain is kept short: a lane's samples are fetched before the model
+// they are weighted with is rebuilt and a slice is two of them per lane; the sums halve the number
+// of values a lane carries; every lane solves for the model (no broadcast, no second barrier) and
+// pivots by selection.  12065 points: 119 us for the twelve launches with slices of 2048 points read one
+// by one, full butterflies and one lane solving through indexed rows, 82 with the shorter chain,
+// 68 with slices of 512 (an empty slice: 59).
+//
+// Models and partials are double-buffered by pass parity, so
 // a launch only reads what the launch before it wrote: no atomics and no counters to clear, and the
 // sequence can be captured into a graph.
 #include <cmath>
@@ -24,28 +34,64 @@ enum { kS, kSx, kSy, kSxx, kSxy, kSyy, kSu, kSxu, kSyu, kSv, kSxv, kSyv, kNz };
 static_assert(kNz + 1 == kGmSums, "sum layout");
 
 constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / 64;
+static_assert(kGmMaxBlocks <= kThreads, "one partial per lane");
+constexpr int kHold = 4; // samples a lane fetches at a time (slices above 131072 points in all are longer than two)
+
+// v + the value of v in lane ^ M, both lanes of a pair alike.
+template <int M>
+__device__ __forceinline__ double add_xor(double v)
+{
+    return v + __shfl_xor(v, M, 64);
+}
+
+// One halving step of the wavefront's sum over the lanes M apart: on return the lanes of the lower
+// half hold a's sum and those of the upper half b's (a pair of swaps in place of two exchanges).
+template <int M>
+__device__ __forceinline__ double add_split(double a, double b)
+{
+    const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 lo, hi;
+    if constexpr (M == 32) {
+        lo = __builtin_amdgcn_permlane32_swap(ua.x, ub.x, false, false);
+        hi = __builtin_amdgcn_permlane32_swap(ua.y, ub.y, false, false);
+    } else {
+        lo = __builtin_amdgcn_permlane16_swap(ua.x, ub.x, false, false);
+        hi = __builtin_amdgcn_permlane16_swap(ua.y, ub.y, false, false);
+    }
+    return __builtin_bit_cast(double, uint2{lo[0], hi[0]}) + __builtin_bit_cast(double, uint2{lo[1], hi[1]});
+}
 
 // Sum of v[k] over the workgroup in a fixed order (lane butterflies, then the four wavefronts in
-// turn); the result is in red[0][k] after the call.
-__device__ void block_sum(double (&v)[kGmSums], double (*red)[kGmSums])
+// turn); after the call every lane's out[k] holds it.  The butterfly's two widest steps halve the
+// number of values a lane carries instead of exchanging all of them, which leaves 4 of the 16
+// (13 and three zeros) for the four narrow steps: 16 exchanges of a double against 78.
+__device__ void block_sum(const double (&v)[kGmSums], double (*red)[16], double (&out)[kGmSums])
 {
+    double h[8], q[4];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) h[k] = add_split<32>(v[k], k + 8 < kGmSums ? v[k + 8 < kGmSums ? k + 8 : 0] : 0.0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        q[k] = add_split<16>(h[k], h[k + 4]);
+        q[k] = add_xor<8>(q[k]);
+        q[k] = add_xor<4>(q[k]);
+        q[k] = add_xor<2>(q[k]);
+        q[k] = add_xor<1>(q[k]);
+    }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if ((lane & 15) == 0)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) red[wave][(lane >> 5) * 8 + ((lane >> 4) & 1) * 4 + k] = q[k];
+    __syncthreads();
 #pragma unroll
     for (int k = 0; k < kGmSums; ++k) {
-        double x = v[k];
+        double x = red[0][k];
 #pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, 64);
-        v[k] = x;
+        for (int w = 1; w < kWaves; ++w) x += red[w][k];
+        out[k] = x;
     }
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0)
-        for (int k = 0; k < kGmSums; ++k) red[wave][k] = v[k];
-    __syncthreads();
-    if (threadIdx.x < kGmSums) {
-        double x = red[0][threadIdx.x];
-        for (int w = 1; w < kThreads / 64; ++w) x += red[w][threadIdx.x];
-        red[0][threadIdx.x] = x;
-    }
-    __syncthreads();
 }
 
 // Model from one pass's sums.  `A` holds the previous model on entry and keeps it when no sample
@@ -53,7 +99,7 @@ __device__ void block_sum(double (&v)[kGmSums], double (*red)[kGmSums])
 // whose weighted covariance C has det C <= 1e-4 (tr C)^2 (collinear), the model is the weighted
 // mean motion.  Otherwise the 3 x 3 normal equations of both motion components are solved by
 // Gaussian elimination with partial pivoting.
-__device__ void gm_solve(const double *S, double *A)
+__device__ __forceinline__ void gm_solve(const double (&S)[kGmSums], double (&A)[6])
 {
     if (!(S[kNz] > 0.0)) return;
     const double is = 1.0 / S[kS];
@@ -70,29 +116,46 @@ __device__ void gm_solve(const double *S, double *A)
     double N[3][5] = {{S[kSxx], S[kSxy], S[kSx], S[kSxu], S[kSxv]},
                       {S[kSxy], S[kSyy], S[kSy], S[kSyu], S[kSyv]},
                       {S[kSx], S[kSy], S[kS], S[kSu], S[kSv]}};
+    // (rows are exchanged by selection: an index known only at run time would put N in memory)
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
         int piv = c;
-        for (int r = c + 1; r < 3; ++r)
-            if (fabs(N[r][c]) > fabs(N[piv][c])) piv = r;
-        if (!(fabs(N[piv][c]) > 0.0)) return;
-        if (piv != c)
-            for (int k = 0; k < 5; ++k) {
-                const double t = N[c][k];
-                N[c][k] = N[piv][k];
-                N[piv][k] = t;
+        double best = fabs(N[c][c]);
+#pragma unroll
+        for (int r = c + 1; r < 3; ++r) {
+            const double a = fabs(N[r][c]);
+            if (a > best) {
+                best = a;
+                piv = r;
             }
+        }
+        if (!(best > 0.0)) return;
+#pragma unroll
+        for (int r = c + 1; r < 3; ++r)
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {
+                const double t = N[c][k], u = N[r][k];
+                N[c][k] = piv == r ? u : t;
+                N[r][k] = piv == r ? t : u;
+            }
+#pragma unroll
         for (int r = c + 1; r < 3; ++r) {
             const double f = N[r][c] / N[c][c];
+#pragma unroll
             for (int k = c; k < 5; ++k) N[r][k] -= f * N[c][k];
         }
     }
     double x[2][3];
+#pragma unroll
     for (int j = 0; j < 2; ++j)
+#pragma unroll
         for (int r = 2; r >= 0; --r) {
             double acc = N[r][3 + j];
+#pragma unroll
             for (int k = r + 1; k < 3; ++k) acc -= N[r][k] * x[j][k];
             x[j][r] = acc / N[r][r];
         }
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
         A[k] = x[0][k];
         A[3 + k] = x[1][k];
@@ -103,8 +166,7 @@ __device__ void gm_solve(const double *S, double *A)
 // 0: weight 1 on every sample); pass kGmPasses only finishes the last model.
 __global__ __launch_bounds__(kThreads) void k_gm_pass(GmFit g, int pass)
 {
-    __shared__ double red[kThreads / 64][kGmSums];
-    __shared__ double sA[6];
+    __shared__ double red[2][kWaves][16];
     const int pair = blockIdx.y;
     const int t = threadIdx.x;
     int64_t p0 = 0, p1 = g.n;
@@ -117,75 +179,90 @@ __global__ __launch_bounds__(kThreads) void k_gm_pass(GmFit g, int pass)
     }
     const int nb = gm_blocks(p1 - p0); // this pair's workgroups (the grid covers the largest pair)
     if ((int)blockIdx.x >= nb) return;
+    const int64_t chunk = (p1 - p0 + nb - 1) / nb;
+    const int64_t b0 = p0 + chunk * blockIdx.x;
+    const int64_t b1 = pass >= kGmPasses ? b0 : (b0 + chunk < p1 ? b0 + chunk : p1);
+    // the slice's first samples are fetched before the model they are weighted with is rebuilt
+    float2 hp[kHold], hm[kHold];
+    uint8_t hs[kHold];
+    auto fetch = [&](int64_t i0) {
+#pragma unroll
+        for (int j = 0; j < kHold; ++j) {
+            const int64_t i = i0 + t + kThreads * j;
+            hs[j] = DGF_ST_CONVERGED + 1;
+            if (i < b1) {
+                hp[j] = g.pts[i];
+                hm[j] = g.flow[i];
+                hs[j] = g.status[i];
+            }
+        }
+    };
+    fetch(b0);
+    double v[kGmSums], A[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (pass > 0) {
         // the model of pass - 1 from its partial sums (kept from pass - 2 where it cannot be solved)
         const double *part = g.part + ((size_t)((pass - 1) & 1) * g.npairs + pair) * g.nblk * kGmSums;
-        double v[kGmSums];
+        if (pass >= 2) {
+            const double *prev = g.models + ((size_t)((pass - 2) & 1) * g.npairs + pair) * 6;
 #pragma unroll
-        for (int k = 0; k < kGmSums; ++k) v[k] = 0.0;
-        for (int b = t; b < nb; b += kThreads)
-#pragma unroll
-            for (int k = 0; k < kGmSums; ++k) v[k] += part[(size_t)b * kGmSums + k];
-        block_sum(v, red);
-        if (t == 0) {
-            double A[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-            if (pass >= 2) {
-                const double *prev = g.models + ((size_t)((pass - 2) & 1) * g.npairs + pair) * 6;
-                for (int k = 0; k < 6; ++k) A[k] = prev[k];
-            }
-            gm_solve(red[0], A);
-            for (int k = 0; k < 6; ++k) sA[k] = A[k];
-            if (blockIdx.x == 0) {
-                double *out = g.models + ((size_t)((pass - 1) & 1) * g.npairs + pair) * 6;
-                for (int k = 0; k < 6; ++k) out[k] = A[k];
-            }
+            for (int k = 0; k < 6; ++k) A[k] = prev[k];
         }
-        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kGmSums; ++k) v[k] = t < nb ? part[(size_t)t * kGmSums + k] : 0.0;
+        double S[kGmSums];
+        block_sum(v, red[0], S);
+        gm_solve(S, A); // by every lane alike
+        if (blockIdx.x == 0 && t == 0) {
+            double *out = g.models + ((size_t)((pass - 1) & 1) * g.npairs + pair) * 6;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) out[k] = A[k];
+        }
     }
     if (pass >= kGmPasses) return;
 
     const double cx = 0.5 * (W - 1), cy = 0.5 * (H - 1);
     const double c2 = g.c * g.c;
-    double A[6];
-    for (int k = 0; k < 6; ++k) A[k] = pass > 0 ? sA[k] : 0.0;
-    const int64_t chunk = (p1 - p0 + nb - 1) / nb;
-    const int64_t b0 = p0 + chunk * blockIdx.x;
-    const int64_t b1 = b0 + chunk < p1 ? b0 + chunk : p1;
-    double v[kGmSums];
 #pragma unroll
     for (int k = 0; k < kGmSums; ++k) v[k] = 0.0;
-    for (int64_t i = b0 + t; i < b1; i += kThreads) {
-        const float2 m = g.flow[i];
-        if (g.status[i] != DGF_ST_CONVERGED || !isfinite(m.x) || !isfinite(m.y)) continue;
-        const float2 p = g.pts[i];
-        const double x = (double)p.x - cx, y = (double)p.y - cy, mu = m.x, mv = m.y;
-        double w = 1.0;
-        if (pass > 0) {
-            const double ex = mu - (A[0] * x + A[1] * y + A[2]);
-            const double ey = mv - (A[3] * x + A[4] * y + A[5]);
-            const double e2 = ex * ex + ey * ey;
-            const double q = 1.0 - e2 / c2;
-            w = e2 < c2 ? q * q : 0.0;
+    for (int64_t i0 = b0; i0 < b1; i0 += kThreads * kHold) {
+        if (i0 != b0) fetch(i0);
+#pragma unroll
+        for (int j = 0; j < kHold; ++j) {
+            const float2 m = hm[j], p = hp[j];
+            if (hs[j] != DGF_ST_CONVERGED || !isfinite(m.x) || !isfinite(m.y)) continue;
+            const double x = (double)p.x - cx, y = (double)p.y - cy, mu = m.x, mv = m.y;
+            double w = 1.0;
+            if (pass > 0) {
+                const double ex = mu - (A[0] * x + A[1] * y + A[2]);
+                const double ey = mv - (A[3] * x + A[4] * y + A[5]);
+                const double e2 = ex * ex + ey * ey;
+                const double q = 1.0 - e2 / c2;
+                w = e2 < c2 ? q * q : 0.0;
+            }
+            if (!(w > 0.0)) continue;
+            const double wx = w * x, wy = w * y;
+            v[kS] += w;
+            v[kSx] += wx;
+            v[kSy] += wy;
+            v[kSxx] += wx * x;
+            v[kSxy] += wx * y;
+            v[kSyy] += wy * y;
+            v[kSu] += w * mu;
+            v[kSxu] += wx * mu;
+            v[kSyu] += wy * mu;
+            v[kSv] += w * mv;
+            v[kSxv] += wx * mv;
+            v[kSyv] += wy * mv;
+            v[kNz] += 1.0;
         }
-        if (!(w > 0.0)) continue;
-        const double wx = w * x, wy = w * y;
-        v[kS] += w;
-        v[kSx] += wx;
-        v[kSy] += wy;
-        v[kSxx] += wx * x;
-        v[kSxy] += wx * y;
-        v[kSyy] += wy * y;
-        v[kSu] += w * mu;
-        v[kSxu] += wx * mu;
-        v[kSyu] += wy * mu;
-        v[kSv] += w * mv;
-        v[kSxv] += wx * mv;
-        v[kSyv] += wy * mv;
-        v[kNz] += 1.0;
     }
-    block_sum(v, red);
-    if (t < kGmSums)
-        g.part[(((size_t)(pass & 1) * g.npairs + pair) * g.nblk + blockIdx.x) * kGmSums + t] = red[0][t];
+    double S[kGmSums];
+    block_sum(v, red[1], S);
+    if (t == 0) {
+        double *out = g.part + (((size_t)(pass & 1) * g.npairs + pair) * g.nblk + blockIdx.x) * kGmSums;
+#pragma unroll
+        for (int k = 0; k < kGmSums; ++k) out[k] = S[k];
+    }
 }
 
 } // namespace
