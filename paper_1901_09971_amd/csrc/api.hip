@@ -220,8 +220,9 @@ int dgf_detect_pyramids(const dgf_image *I0, const dgf_image *I1, int32_t window
     D.stride = stride;
     D.nx = (D.W - window) / stride + 1;
     D.ny = (D.H - window) / stride + 1;
-    D.tiles_x = (D.nx + 15) / 16;
-    D.tiles_y = (D.ny + 15) / 16;
+    D.side = detect_tile_side(window, stride);
+    D.tiles_x = (D.nx + D.side - 1) / D.side;
+    D.tiles_y = (D.ny + D.side - 1) / D.side;
     D.o = DetectOut{points, sel, response};
     return hip_rc(launch_pyr_chains(srcs, sp, lvl, pitch, I0->width, I0->height, levels, 2, DGF_U8, st, &D));
 }

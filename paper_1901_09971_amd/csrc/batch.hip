@@ -190,7 +190,7 @@ int dgf_batch_create(const dgf_pair_desc *pairs, int32_t npairs, int32_t levels,
     const int orc = effective_track_opts(opts, support, &o);
     if (orc != DGF_OK) return orc;
     for (int i = 0; i < npairs; ++i)
-        if (front_detect_lds(pairs[i].window, pairs[i].stride) > kMaxLdsPerBlock) return DGF_ERR_UNSUPPORTED;
+        if (!front_detect_takes(pairs[i].window, pairs[i].stride)) return DGF_ERR_UNSUPPORTED;
 
     dgf_batch *b = new (std::nothrow) dgf_batch();
     if (!b) return DGF_ERR_INVALID_ARG;

@@ -533,15 +533,91 @@ __device__ __forceinline__ void finish_window(int S, int Mi, int Mj, int m, int 
     if (o.resp) o.resp[n] = d.resp;
 }
 
+// Sums over one window row, four bytes at a time with byte dot products.  `p` is the aligned LDS
+// dword holding the row's first byte, which is byte `sh` of it; `last` is the index of the dword
+// holding the row's last byte (nothing past it is read).  S and J take the sum and the column moment;
+// mx collects maxima per pair of bytes -- the odd bytes in place (the even byte below cannot
+// change their order) in mx[0], the even ones moved up in mx[1]; window_max gives the maximum.
+// ND = ceil(win / 4) fixes the number of steps (0: any).
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+template <int ND>
+__device__ __forceinline__ void window_row(const uint32_t *p, int last, uint32_t sh, int win, uint32_t &S, uint32_t &J,
+                                           u16x2 (&mx)[2])
+{
+    const int nd = ND > 0 ? ND : (win + 3) >> 2;
+    const uint32_t keep = 0xffffffffu >> (8 * (4 * nd - win)); // the last dword's bytes inside the row
+    constexpr uint32_t kOnes = 0x01010101u, kIdx = 0x03020100u;
+    auto step = [&](int k, uint32_t lo, uint32_t hi, uint32_t m) {
+        const uint32_t v = __builtin_amdgcn_alignbyte(hi, lo, sh);
+        if constexpr (ND > 0 && ND <= 63) { // (columns 4 k .. 4 k + 3 fit a byte)
+            S = __builtin_amdgcn_udot4(v, kOnes & m, S, false);
+            J = __builtin_amdgcn_udot4(v, (kIdx + 4u * (uint32_t)k * kOnes) & m, J, false);
+        } else {
+            const uint32_t t = __builtin_amdgcn_udot4(v, kOnes & m, 0u, false);
+            S += t;
+            J = __builtin_amdgcn_udot4(v, kIdx & m, J, false) + 4u * (uint32_t)k * t;
+        }
+        const u16x2 o = __builtin_bit_cast(u16x2, v & m);
+        mx[0] = __builtin_elementwise_max(mx[0], o);
+        mx[1] = __builtin_elementwise_max(mx[1], (u16x2)(o << (u16x2)8));
+    };
+    if constexpr (ND > 0) {
+        uint32_t d[ND + 1];
+#pragma unroll
+        for (int k = 0; k < ND; ++k) d[k] = p[k];
+        d[ND] = p[last];
+#pragma unroll
+        for (int k = 0; k < ND; ++k) step(k, d[k], d[k + 1], k == ND - 1 ? keep : 0xffffffffu);
+    } else {
+        uint32_t lo = p[0];
+        for (int k = 0; k < nd - 1; ++k) {
+            const uint32_t hi = p[k + 1];
+            step(k, lo, hi, 0xffffffffu);
+            lo = hi;
+        }
+        step(nd - 1, lo, p[last], keep);
+    }
+}
+
+__device__ __forceinline__ int window_max(const u16x2 (&mx)[2])
+{
+    const u16x2 m = __builtin_elementwise_max(mx[0], mx[1]);
+    return max((int)m[0], (int)m[1]) >> 8;
+}
+
+// f(ND, WIN) for this window: 9 (the paper's) and 3 (the smallest) with their row loops unrolled,
+// the others up to 12 with their step count alone
+template <class F>
+__device__ __forceinline__ void with_window(int win, F f)
+{
+    using std::integral_constant;
+    if (win == 9)
+        f(integral_constant<int, 3>(), integral_constant<int, 9>());
+    else if (win == 3)
+        f(integral_constant<int, 1>(), integral_constant<int, 3>());
+    else if (win <= 4)
+        f(integral_constant<int, 1>(), integral_constant<int, 0>());
+    else if (win <= 8)
+        f(integral_constant<int, 2>(), integral_constant<int, 0>());
+    else if (win <= 12)
+        f(integral_constant<int, 3>(), integral_constant<int, 0>());
+    else
+        f(integral_constant<int, 0>(), integral_constant<int, 0>());
+}
+
 // LDS-tiled form: TX x TY windows per workgroup (tile (tile_x, tile_y) of the window grid), one
 // lane per window, the covered pixels staged in `tile` (row pitch rounded up to 4 bytes, 4-byte
 // aligned).  n0 offsets the output (batched form: points of a pair start at its offset in the
-// concatenated output).
-template <int TX, int TY>
-__device__ __forceinline__ void detect_tile(uint8_t *tile, int tile_x, int tile_y, const uint8_t *__restrict__ img,
-                                            int64_t pitch, int W, int H, int win, int stride, int nx, int ny, int64_t n0,
-                                            DetectOut o)
+// concatenated output).  The row moment needs no sum of its own: sum_i i r_i = (w - 1) S - the sums
+// through each row but the last.
+template <int TX, int TY, int ND, int WIN>
+__device__ __forceinline__ void detect_tile_nd(uint8_t *tile, int tile_x, int tile_y, const uint8_t *__restrict__ img,
+                                                int64_t pitch, int W, int H, int win, int stride, int nx, int ny,
+                                                int64_t n0, DetectOut o)
 {
+    if constexpr (WIN > 0) win = WIN;
+    constexpr int kRows = WIN > 0 ? WIN : 3; // rows per unrolled step
     const int wx0 = tile_x * TX, wy0 = tile_y * TY;
     const int ox = wx0 * stride, oy = wy0 * stride;
     const int RW = (TX - 1) * stride + win, RH = (TY - 1) * stride + win, RP = (RW + 3) & ~3;
@@ -551,21 +627,99 @@ __device__ __forceinline__ void detect_tile(uint8_t *tile, int tile_x, int tile_
     const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
     const int kx = wx0 + tx, ky = wy0 + ty;
     if (ty >= TY || kx >= nx || ky >= ny) return; // (blocks may have more lanes than windows)
-    const uint8_t *w0 = tile + ty * stride * RP + tx * stride;
-    int S = 0, Mi = 0, Mj = 0, m = 0;
+    const uint32_t sh = (uint32_t)(tx * stride) & 3u;
+    const uint32_t *p = reinterpret_cast<const uint32_t *>(tile) + ((ty * stride * RP + tx * stride) >> 2);
+    const int last = (int)(sh + win - 1) >> 2;
+    uint32_t S = 0u, T = 0u, J = 0u;
+    u16x2 mx[2] = {(u16x2)0, (u16x2)0};
+#pragma unroll kRows
     for (int i = 0; i < win; ++i) {
-        int rs = 0, rj = 0;
-        for (int j = 0; j < win; ++j) {
-            const int v = w0[i * RP + j];
-            rs += v;
-            rj += j * v;
-            m = max(m, v);
-        }
-        S += rs;
-        Mi += i * rs;
-        Mj += rj;
+        T += S;
+        window_row<ND>(p + i * (RP >> 2), last, sh, win, S, J, mx);
     }
-    finish_window(S, Mi, Mj, m, win, kx * stride, ky * stride, n0 + (int64_t)ky * nx + kx, o);
+    finish_window((int)S, (int)((uint32_t)(win - 1) * S - T), (int)J, window_max(mx), win, kx * stride, ky * stride,
+                  n0 + (int64_t)ky * nx + kx, o);
+}
+
+template <int TX, int TY>
+__device__ __forceinline__ void detect_tile(uint8_t *tile, int tile_x, int tile_y, const uint8_t *__restrict__ img,
+                                            int64_t pitch, int W, int H, int win, int stride, int nx, int ny, int64_t n0,
+                                            DetectOut o)
+{
+    with_window(win, [&](auto nd, auto w) {
+        detect_tile_nd<TX, TY, nd.value, w.value>(tile, tile_x, tile_y, img, pitch, W, H, win, stride, nx, ny, n0, o);
+    });
+}
+
+// Row-sum form for windows that overlap much: per staged row and window column the sums over the
+// window's width, then per window the sums of those over its rows -- rows shared by windows one
+// above the other are summed once.  With n = ceil(w / 4) steps per row that is about 7 n stride + 6 w
+// + 20 operations per window against (7 n + 2) w for each window by itself: it pays from three
+// windows per pixel row and two steps on.  With less overlap its larger tile still pays once the
+// grid fills the chip (`many`: a workgroup per CU; a batch plan always does): window 3, stride 1 at 4096x2160
+// 41 us against 60, at 640x480 4.9 against 4.8.  A tile is 16 x 32 windows, or 16 x 16 at stride 3
+// (its pixels are then still fetched in one round: 1242x375, window 9, 6.0 -> 4.3 us), by 256 lanes.  LDS: the staged
+// pixels (row pitch RP bytes, RH rows), then [RH][16] pairs of dwords: sum (up to 255 w) with the
+// maximum above it in 16 bits each, and the column moment.
+inline __host__ __device__ bool detect_by_rows(int win, int stride, bool many)
+{
+    return stride <= 3 && win <= 256 && ((win >= 3 * stride && win > 4) || (many && stride < win));
+}
+inline __host__ __device__ int detect_rows_high(int stride) { return stride < 3 ? 32 : 16; } // windows
+
+inline __host__ __device__ size_t detect_rows_lds(int win, int stride)
+{
+    const size_t RW = (size_t)(15 * stride + win), RH = (size_t)((detect_rows_high(stride) - 1) * stride + win);
+    const size_t RP = (RW + 3) & ~(size_t)3;
+    return ((RP * RH + 15) & ~(size_t)15) + 2 * RH * 16 * sizeof(uint32_t);
+}
+
+template <int ND, int WIN>
+__device__ __forceinline__ void detect_tile_rows(uint8_t *lds, int tile_x, int tile_y, const uint8_t *__restrict__ img,
+                                                 int64_t pitch, int W, int H, int win, int stride, int nx, int ny,
+                                                 int64_t n0, DetectOut o)
+{
+    if constexpr (WIN > 0) win = WIN;
+    constexpr int kRows = WIN > 0 ? WIN : 3; // rows per unrolled step
+    const int s = stride, high = detect_rows_high(stride);
+    const int wx0 = tile_x * 16, wy0 = tile_y * high;
+    const int ox = wx0 * s, oy = wy0 * s;
+    const int RW = 15 * s + win, RH = (high - 1) * s + win, RP = (RW + 3) & ~3;
+    const int rw = min(RW, W - ox), rh = min(RH, H - oy);
+    stage_u8_block<4>(lds, RP, img, pitch, W, ox, oy, rw, rh);
+    uint2 *hsum = reinterpret_cast<uint2 *>(lds + ((RP * RH + 15) & ~15));
+    __syncthreads();
+    {
+        const int c = threadIdx.x & 15;
+        const uint32_t sh = (uint32_t)(c * s) & 3u;
+        const int last = (int)(sh + win - 1) >> 2;
+        // (window columns past the grid's end would read pixels that were not staged)
+        if (c * s + win <= rw)
+            for (int r = threadIdx.x >> 4; r < rh; r += 16) {
+                uint32_t S = 0u, J = 0u;
+                u16x2 mx[2] = {(u16x2)0, (u16x2)0};
+                window_row<ND>(reinterpret_cast<const uint32_t *>(lds) + ((r * RP + c * s) >> 2), last, sh, win, S, J, mx);
+                hsum[r * 16 + c] = make_uint2(S | ((uint32_t)window_max(mx) << 16), J);
+            }
+    }
+    __syncthreads();
+    for (int ty = threadIdx.x >> 4; ty < high; ty += 16) {
+        const int tx = threadIdx.x & 15;
+        const int kx = wx0 + tx, ky = wy0 + ty;
+        if (kx >= nx || ky >= ny) continue;
+        uint32_t S = 0u, T = 0u, J = 0u, m = 0u;
+        const uint2 *p = hsum + ty * s * 16 + tx;
+#pragma unroll kRows
+        for (int i = 0; i < win; ++i) {
+            const uint2 v = p[i * 16];
+            T += S;
+            S += v.x & 0xffffu;
+            J += v.y;
+            m = max(m, v.x); // ordered by the maximum in the upper half
+        }
+        finish_window((int)S, (int)((uint32_t)(win - 1) * S - T), (int)J, (int)(m >> 16), win, kx * s, ky * s,
+                      n0 + (int64_t)ky * nx + kx, o);
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -895,6 +1049,7 @@ struct DetectJob {
 
 // launchers (return hipSuccess or the launch error)
 size_t detect_tile_lds(int win, int stride);
+int detect_tile_side(int win, int stride); // windows per tile side of a single frame's detection, 8 or 16
 hipError_t launch_detect(const uint8_t *img, int64_t pitch, int W, int H, int win, int stride, float *pts,
                          uint8_t *sel, float *resp, hipStream_t st);
 
@@ -910,12 +1065,12 @@ struct PyrChain {
     int32_t m;
 };
 // Detection of one uint8 frame run beside the first pyramid-chain launch (dgf_detect_pyramids):
-// tiles_x x tiles_y tiles of 16 x 16 windows; front_detect_fits tells whether a tile's pixels fit
+// tiles_x x tiles_y tiles of side x side windows; front_detect_fits tells whether a tile's pixels fit
 // the chain's LDS.
 struct FrontDetect {
     const uint8_t *img;
     int64_t pitch;
-    int32_t W, H, win, stride, nx, ny, tiles_x, tiles_y;
+    int32_t W, H, win, stride, nx, ny, tiles_x, tiles_y, side;
     DetectOut o;
 };
 // The front end of a batch plan (front_batch.hip): level 1 of every frame beside every pair's
@@ -930,6 +1085,7 @@ struct BatchFront {
 };
 hipError_t launch_front_batched(const BatchFront &F, float *pts, hipStream_t st);
 size_t front_detect_lds(int win, int stride); // LDS of one pair's detection tile in that launch
+bool front_detect_takes(int win, int stride); // whether a batch plan takes this window
 
 bool front_detect_fits(int win, int stride);
 hipError_t launch_pyr_chain_u8(const PyrChain &A, int njobs, hipStream_t st, const FrontDetect *det = nullptr);

@@ -6,17 +6,15 @@
 // is one launch over all frames.  (Chains of four levels per launch, as the single-pair front end
 // uses, measured 5x slower here: tens of thousands of small latency-bound workgroups.)  The
 // uint8 arithmetic is that of
-// k_pyr_down and of detect_tile -- exact integer sums, (sum + 128) >> 8 per level, replicated
+// the chain and of detect_tile -- exact integer sums, (sum + 128) >> 8 per level, replicated
 // borders -- so the outputs are bit-identical to theirs; only the data movement and the
 // instruction count differ:
 //   * pyramid: a workgroup makes 128 x 16 output pixels from a 264 x 35 byte rectangle staged as
 //     dwords; the horizontal 5-tap pass takes four outputs from four dwords with byte dot
 //     products (weights 1 4 6 4, plus the fifth tap), the vertical pass works on pairs of 16-bit
 //     sums and writes four output bytes per store;
-//   * detection at strides up to 3: per staged row and window column the row sums over the
-//     window width (sum, column moment, maximum), then per window the sums of those over its
-//     rows -- about (3 + 4) w operations per window and row of windows instead of 4 w^2 per
-//     window; at larger strides the windows barely overlap and detect_tile sums each window.
+//   * detection: the tiles of single-frame detection (row sums where windows overlap, else a window
+//     per lane).
 #include "dgf_internal.hpp"
 
 namespace dgf {
@@ -29,8 +27,6 @@ constexpr int PF_IP = PF_IWD + 2;            // their LDS row pitch in dwords
 constexpr int PF_IH = 2 * PF_OH + 3;         // staged rows 2 oy - 2 .. 2 oy + 2 OH
 constexpr int PF_HP = PF_OW / 2;             // horizontal sums per row, two 16-bit sums per dword
 constexpr size_t kPyrLds = (size_t)(PF_IH * PF_IP + PF_IH * PF_HP) * 4;
-
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 // One 128 x 16 tile of the next level of a uint8 image.  Staging: each lane fetches its ten dwords
 // of the 264 x 35 byte rectangle before writing any of them to LDS, so the loads are in flight
@@ -127,79 +123,6 @@ __device__ void pyr_tile_fast(const PyrJob &J, int tile_x, int tile_y, uint32_t 
     }
 }
 
-// Separable detection of one tile of 16 x 32 windows (same windows, sums and outputs as
-// detect_tile; two windows per lane).  lds: the staged pixels (row pitch RP bytes, RH rows), then
-// three [RH][16] int arrays of row sums over each window column.
-constexpr int kSepRows = 32; // window rows per separable tile
-
-template <int WIN>
-__device__ void detect_tile_rows(uint8_t *lds, int tile_x, int tile_y, const DetectJob &J, DetectOut o, int win)
-{
-    if constexpr (WIN > 0) win = WIN;
-    const int s = J.stride;
-    const int wx0 = tile_x * 16, wy0 = tile_y * kSepRows;
-    const int ox = wx0 * s, oy = wy0 * s;
-    const int RW = 15 * s + win, RH = (kSepRows - 1) * s + win, RP = (RW + 3) & ~3;
-    const int rw = min(RW, J.W - ox), rh = min(RH, J.H - oy);
-    stage_u8_block<4>(lds, RP, J.img, J.pitch, J.W, ox, oy, rw, rh);
-    int *hS = reinterpret_cast<int *>(lds + ((RP * RH + 15) & ~15));
-    int *hJ = hS + RH * 16, *hM = hJ + RH * 16;
-    __syncthreads();
-    for (int t = (int)threadIdx.x; t < rh * 16; t += 256) {
-        const int r = t >> 4, c = t & 15;
-        const uint8_t *p = lds + r * RP + c * s;
-        int sum = 0, mom = 0, mx = 0;
-#pragma unroll
-        for (int j = 0; j < (WIN > 0 ? WIN : 1); ++j) {
-            if constexpr (WIN > 0) {
-                const int v = p[j];
-                sum += v;
-                mom += j * v;
-                mx = max(mx, v);
-            }
-        }
-        if constexpr (WIN == 0) {
-            for (int j = 0; j < win; ++j) {
-                const int v = p[j];
-                sum += v;
-                mom += j * v;
-                mx = max(mx, v);
-            }
-        }
-        hS[t] = sum;
-        hJ[t] = mom;
-        hM[t] = mx;
-    }
-    __syncthreads();
-    for (int h = 0; h < kSepRows / 16; ++h) {
-    const int tx = threadIdx.x & 15, ty = (threadIdx.x >> 4) + 16 * h;
-    const int kx = wx0 + tx, ky = wy0 + ty;
-    if (kx >= J.nx || ky >= J.ny) continue;
-    int S = 0, Mi = 0, Mj = 0, m = 0;
-    const int b = ty * s * 16 + tx;
-#pragma unroll
-    for (int i = 0; i < (WIN > 0 ? WIN : 1); ++i) {
-        if constexpr (WIN > 0) {
-            const int rs = hS[b + i * 16];
-            S += rs;
-            Mi += i * rs;
-            Mj += hJ[b + i * 16];
-            m = max(m, hM[b + i * 16]);
-        }
-    }
-    if constexpr (WIN == 0) {
-        for (int i = 0; i < win; ++i) {
-            const int rs = hS[b + i * 16];
-            S += rs;
-            Mi += i * rs;
-            Mj += hJ[b + i * 16];
-            m = max(m, hM[b + i * 16]);
-        }
-    }
-    finish_window(S, Mi, Mj, m, win, kx * s, ky * s, J.out_off + (int64_t)ky * J.nx + kx, o);
-    }
-}
-
 // Level 1 of every frame (blocks 0 .. npyr - 1: frame b / per_frame, tile b mod per_frame of a
 // tiles_x-wide grid) beside every pair's detection (the rest: pair, then tile of a det_tx-wide
 // grid).  Tiles beyond a frame's or a pair's extent exit at once.
@@ -216,22 +139,21 @@ __global__ __launch_bounds__(256) void k_front_batched(const PyrJob *__restrict_
         pyr_tile_fast(J, tx, ty, reinterpret_cast<uint32_t *>(smem));
         return;
     }
-    // (the grid counts 16 x 16 tiles; a separable tile takes two rows of them, the odd row exits)
+    // (the grid counts 16 x 16 tiles; a row-sum tile of 32 takes two rows of them, the odd row exits)
     const int bd = b - npyr, p = bd / per_pair, t = bd - p * per_pair, ty = t / det_tx, tx = t - ty * det_tx;
     const DetectJob J = det[p];
     if (tx * 16 >= J.nx || ty * 16 >= J.ny) return;
     const DetectOut o{pts, nullptr, nullptr};
-    if (J.stride > 3 || J.stride >= J.win) { // little overlap between windows: per-window sums
+    if (!detect_by_rows(J.win, J.stride, true)) { // little overlap between windows: per-window sums
         detect_tile<16, 16>(smem, tx, ty, J.img, J.pitch, J.W, J.H, J.win, J.stride, J.nx, J.ny, J.out_off, o);
         return;
     }
-    if (ty & 1) return;
-    if (J.win == 9)
-        detect_tile_rows<9>(smem, tx, ty >> 1, J, o, 9);
-    else if (J.win == 3)
-        detect_tile_rows<3>(smem, tx, ty >> 1, J, o, 3);
-    else
-        detect_tile_rows<0>(smem, tx, ty >> 1, J, o, J.win);
+    const int per = detect_rows_high(J.stride) / 16;
+    if (ty % per) return;
+    with_window(J.win, [&](auto nd, auto w) {
+        detect_tile_rows<nd.value, w.value>(smem, tx, ty / per, J.img, J.pitch, J.W, J.H, J.win, J.stride, J.nx, J.ny,
+                                            J.out_off, o);
+    });
 }
 
 // One coarser level of every frame (blockIdx.z = frame).
@@ -247,10 +169,17 @@ __global__ __launch_bounds__(256) void k_pyr_level_batched(const PyrJob *__restr
 
 size_t front_detect_lds(int win, int stride)
 {
-    if (stride > 3 || stride >= win) return detect_tile_lds(win, stride);
-    const size_t RW = (size_t)(15 * stride + win), RH = (size_t)((kSepRows - 1) * stride + win);
+    return detect_by_rows(win, stride, true) ? detect_rows_lds(win, stride) : detect_tile_lds(win, stride);
+}
+
+// A plan takes the windows whose tile and, at the strides summed by rows, three words per row and
+// window column fit a workgroup's LDS (the sums themselves take two).
+bool front_detect_takes(int win, int stride)
+{
+    if (stride > 3 || stride >= win) return detect_tile_lds(win, stride) <= kMaxLdsPerBlock;
+    const size_t RW = (size_t)(15 * stride + win), RH = (size_t)(31 * stride + win);
     const size_t RP = (RW + 3) & ~(size_t)3;
-    return ((RP * RH + 15) & ~(size_t)15) + 3 * RH * 16 * sizeof(int);
+    return ((RP * RH + 15) & ~(size_t)15) + 3 * RH * 16 * sizeof(int) <= kMaxLdsPerBlock;
 }
 
 hipError_t launch_front_batched(const BatchFront &F, float *pts, hipStream_t st)

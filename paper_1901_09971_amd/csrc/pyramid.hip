@@ -122,8 +122,12 @@ __global__ __launch_bounds__(kChainThreads) void k_front_u8(PyrChain A, FrontDet
         return;
     }
     const int t = b - nchain, ty = t / D.tiles_x;
-    detect_tile<16, 16>(&lvl[0][0], t - ty * D.tiles_x, ty, D.img, D.pitch, D.W, D.H, D.win, D.stride, D.nx, D.ny, 0,
-                        D.o);
+    if (D.side == 8)
+        detect_tile<8, 8>(&lvl[0][0], t - ty * D.tiles_x, ty, D.img, D.pitch, D.W, D.H, D.win, D.stride, D.nx, D.ny, 0,
+                          D.o);
+    else
+        detect_tile<16, 16>(&lvl[0][0], t - ty * D.tiles_x, ty, D.img, D.pitch, D.W, D.H, D.win, D.stride, D.nx, D.ny, 0,
+                            D.o);
 }
 
 // Largest detection tile the fused launch can stage (the chain's two level buffers).
