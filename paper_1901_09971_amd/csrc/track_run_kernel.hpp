@@ -106,13 +106,25 @@ __device__ __forceinline__ bool group_any(bool p)
         return wave_any(p);
 }
 
-// The 64-lane form without the illumination model is held to 80 VGPRs (six waves per SIMD): it is
-// issue bound, and the sixth wave pays.  MODE (ROBUST_L2 / HAMPEL / HARD), CROSS (adaptive
+// Waves per SIMD that a shape's registers are held to.  The kernel is issue bound (VALU about nine
+// tenths busy), and one more wave pays where it costs few or no spills: 64 lanes, plain, six (80
+// registers), with the illumination model five (96, seven spilled on uint8: support 21 at 1242x375
+// 378 -> 364 us); 32 lanes and ten pixels, support 15, plain uint8 five (214 -> 207), with the
+// model four (349 -> 329).  32 lanes, support 9 with the model lost by it (216 -> 229, four to
+// thirteen spilled), and 16 lanes are held to three or four waves by LDS.
+constexpr int run_min_waves(int lpp, int ppl, int bytes, bool im)
+{
+    if (lpp == 64) return im ? 5 : 6;
+    if (lpp == 32 && ppl == 10) return im ? 4 : bytes == 1 ? 5 : 1;
+    return 1;
+}
+
+// MODE (ROBUST_L2 / HAMPEL / HARD), CROSS (adaptive
 // cross-based supports) and BATCH (a batch plan's persistent launch rather than one pair) are
 // compile-time, so a single-pair square-window launch carries no batch bookkeeping, no per-pixel
 // support mask and no branch on the robust norm.
 template <int LPP, int SEG, int R, int TP, int S, typename PixT, bool IM, int MODE, bool CROSS, bool BATCH>
-__global__ __launch_bounds__(256, (LPP == 64 && !IM) ? 6 : 1) void k_track_run(TrackParams P)
+__global__ __launch_bounds__(256, run_min_waves(LPP, SEG * R, sizeof(PixT), IM)) void k_track_run(TrackParams P)
 {
     constexpr int PPW = 64 / LPP;
     constexpr int PPL = SEG * R;
