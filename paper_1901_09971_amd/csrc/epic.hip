@@ -677,6 +677,13 @@ __device__ __forceinline__ double wave_sum_f64(double v)
 
 __device__ __forceinline__ int hash_slot(int32_t t) { return (int)(((uint32_t)t * 2654435761u) >> 23); }
 
+// A least edge of up to 16 bits in seven, rounded down: 4 bits of exponent above 3 of mantissa (0: below 2).
+__device__ __forceinline__ uint32_t least_code(uint32_t l)
+{
+    const uint32_t e = 31u - (uint32_t)__builtin_clz(l | 1u);
+    return e == 0u ? 0u : e << 3 | (((l << 3) >> e) & 7u);
+}
+
 // One wavefront per seed s: its k nearest seeds on the seed graph in increasing (distance, index)
 // order, at graph distance <= 64 h, then the weighted least-squares affine model of the flow
 // around s, in FP64.  The search settles in batches: with T the least tentative distance plus
@@ -689,10 +696,11 @@ __device__ __forceinline__ int hash_slot(int32_t t) { return (int)(((uint32_t)t 
 // neighbours, and the rest take further rounds.  RPL: rows of the fit per lane, k <= 64 RPL.
 //
 // The search is a chain of short LDS and L2 round trips with VALU and scalar issue about even between
-// them: LDS is kept to 6.9 KB so that 21 searches share a CU, edges are inserted 64 at a time, nodes
-// are ranked within their batch only, and the fit's first column comes from the moments.  2048x1024,
-// 117,238 seeds, k 128: 2,382 -> 1,026 us (7,185 -> 3,510 VALU and 5,000 -> 2,850 scalar instructions
-// per seed); 1242x375, 9,368 seeds: 246 -> 116 us.  Candidate capacity and results are as before.
+// them: LDS is kept to 6.1 KB so that 25 searches share a CU (at 6.9 KB, with the least edges in 16 bits of
+// their own, 21 did: 1,011 us for 966 below), edges are inserted 64 at a time, nodes are ranked
+// within their batch only, and the fit's first column comes from the moments.  2048x1024, 117,238
+// seeds, k 128: 2,382 -> 966 us (7,185 -> about 3,500 VALU and 5,000 -> 2,850 scalar instructions per
+// seed); 1242x375, 9,368 seeds: 246 -> 116 us.  Candidate capacity and results are as before.
 template <int RPL>
 __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
 {
@@ -703,8 +711,7 @@ __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
     __shared__ int32_t hkey[kHash];   // node, or -1
     __shared__ uint16_t hval[kHash];  // its candidate slot
     __shared__ uint32_t cdist[kCand]; // candidates: tentative distance (all ones past the last one),
-    __shared__ uint16_t chash[kCand]; // place in the hash,
-    __shared__ uint16_t cmin[kCand];  // and least edge, in units of 2^shift (rounded down)
+    __shared__ uint16_t chash[kCand]; // place in the hash, and least edge above it (least_code)
     __shared__ uint16_t sslot[kCand]; // candidate slots of the settled nodes, sorted by (distance, index)
     const int li = threadIdx.x;
     const int64_t s = blockIdx.x;
@@ -719,7 +726,7 @@ __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
     auto before = [](uint64_t mask) { // set bits of the mask in lower lanes
         return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
     };
-    auto node_of = [&](int slot) { return hkey[chash[slot]]; };
+    auto node_of = [&](int slot) { return hkey[chash[slot] & (kHash - 1)]; };
     int cnt = 0;
     bool overflow = false;
     if (alive) {
@@ -730,11 +737,11 @@ __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
             const int h = hash_slot((int32_t)s);
             hkey[h] = (int32_t)s;
             hval[h] = 0;
-            chash[0] = (uint16_t)h;
+            chash[0] = (uint16_t)h; // (no least edge: alone in its batch whatever T is)
             cdist[0] = 0u;
-            cmin[0] = 0; // (alone in its batch whatever T is)
         }
-        // a least edge beyond dmax bounds no more than dmax does, so 16 bits of dmax's scale hold it
+        // a least edge beyond dmax bounds no more than dmax does, so 16 bits of dmax's scale hold it (and
+        // seven its leading ones)
         const int shift = max(0, 16 - __builtin_clz(F.dmax | 1u));
         const uint32_t least_cap = min(F.dmax >> shift, 0xFFFFu);
         int m = 1, first = 0;  // candidates, and the first group of 64 that are not all settled (its slot)
@@ -744,7 +751,8 @@ __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
             // T (distances and least edges are at most dmax <= 2^30, so sums fit)
             uint32_t T = 0xFFFFFFFFu;
             for (int base = first; base < m; base += 64) {
-                const uint32_t d = cdist[base + li], least = max((uint32_t)cmin[base + li] << shift, 1u);
+                const uint32_t d = cdist[base + li], code = (uint32_t)chash[base + li] >> 9;
+                const uint32_t least = code ? (((8u | (code & 7u)) << (code >> 3)) >> 3) << shift : 1u;
                 if (d - settled < 0xFFFFFFFFu - settled) T = min(T, d + least); // settled <= d < all ones
             }
             T = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_min_u32(T));
@@ -833,8 +841,7 @@ __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
                 if (is_new) {
                     const int slot = m + before(nbm);
                     hval[hs] = (uint16_t)slot;
-                    chash[slot] = (uint16_t)hs;
-                    cmin[slot] = (uint16_t)min(least >> shift, least_cap);
+                    chash[slot] = (uint16_t)(hs | least_code(min(least >> shift, least_cap)) << 9);
                 }
                 m += total;
                 __syncthreads();
