@@ -11,6 +11,9 @@
 // onto border pixels).  Only the level-0 images enter: the coarser levels decide which fixed
 // point is reached, not its local dependence on the pixels.
 //
+// The kernels here take any odd support; the supports that the tracker's row-run shapes are compiled
+// for go to adjoint_point.hpp's form (adjoint_tiled.hip, adjoint_direct.hip).
+//
 // One point per wavefront (a one-wave workgroup).  The raw I0 patch (s+3)^2 around the template
 // and the raw I1 patch (s+1)^2 under the tracked position are staged in LDS; lanes stride over the
 // s x s support.  Pass 1 accumulates the four entries of J (wave reduction) and every lane solves
@@ -245,7 +248,6 @@ __global__ __launch_bounds__(64) void k_track_adjoint(AdjParams A)
 //   dI1 -= psi' (mu . phi') beta,
 //   dI0 += [(1 + m) psi' (mu . phi') + psi mu_m / Ts] alpha - (1 + m) psi mu_d . dg/dI0.
 // The image gradients are gathered as in k_track_adjoint, with the sample term A0 apart from c1.
-template <typename PixT>
 __global__ __launch_bounds__(64) void k_track_adjoint_illum(AdjParams A)
 {
     extern __shared__ float smem[];
@@ -274,8 +276,8 @@ __global__ __launch_bounds__(64) void k_track_adjoint_illum(AdjParams A)
 
     const int w0 = s + 3, w1 = s + 1, n0 = w0 * w0, n1 = w1 * w1;
     float *raw0 = smem, *raw1 = smem + n0, *C1 = raw1 + n1, *CX = C1 + S2, *CY = CX + S2, *A0 = CY + S2;
-    stage_rect<64, PixT>(raw0, w0, Pr.I0, Pr.pitch0, W, H, ox0, oy0, w0, w0, stage_lanes<64>(w0, li));
-    stage_rect<64, PixT>(raw1, w1, Pr.I1, Pr.pitch1, W, H, ox1, oy1, w1, w1, stage_lanes<64>(w1, li));
+    stage_rect<64, float>(raw0, w0, Pr.I0, Pr.pitch0, W, H, ox0, oy0, w0, w0, stage_lanes<64>(w0, li));
+    stage_rect<64, float>(raw1, w1, Pr.I1, Pr.pitch1, W, H, ox1, oy1, w1, w1, stage_lanes<64>(w1, li));
     __syncthreads();
     auto I0s = [&](int lx, int ly) { return lerp_cell(raw0 + ly * w0 + lx, w0, fx0, fy0); };
 
@@ -487,12 +489,9 @@ hipError_t launch_track_adjoint(const AdjParams &A0, int dtype, hipStream_t st)
     A.perm_mul = scatter_multiplier(A.n);
     if (adjoint_support_compiled(A.s) && (dtype == DGF_U8) == (A.npairs > 0)) return launch_adjoint_direct(A, st);
     const size_t lds = adjoint_lds_bytes(A.s);
-    if (A.illum) {
-        if (dtype == DGF_U8)
-            hipLaunchKernelGGL(k_track_adjoint_illum<uint8_t>, dim3((unsigned)A.n), dim3(64), lds, st, A);
-        else
-            hipLaunchKernelGGL(k_track_adjoint_illum<float>, dim3((unsigned)A.n), dim3(64), lds, st, A);
-    } else if (dtype == DGF_U8)
+    if (A.illum) // (float pairs only: a plan with the model has a compiled support)
+        hipLaunchKernelGGL(k_track_adjoint_illum, dim3((unsigned)A.n), dim3(64), lds, st, A);
+    else if (dtype == DGF_U8)
         hipLaunchKernelGGL(k_track_adjoint<uint8_t>, dim3((unsigned)A.n), dim3(64), lds, st, A);
     else
         hipLaunchKernelGGL(k_track_adjoint<float>, dim3((unsigned)A.n), dim3(64), lds, st, A);

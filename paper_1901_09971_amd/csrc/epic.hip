@@ -10,9 +10,11 @@
 //   k_epic_prep     edge map (uint16) and cleared tables, HBM bound
 //   k_epic_seed     one 64-bit atomicMin per converged point: key = (0 << 32) | index
 //   k_epic_relax    62x32 tiles relaxed in registers (Bellman-Ford sweeps), exchanging border
-//                   pixels with their neighbours during the launch; launched until a launch
-//                   changes nothing (host checks a counter every few launches)
-//   k_epic_graph    adjacent-cell pairs inserted into fixed-size per-seed adjacency rows
+//                   pixels with their neighbours during the launch; a grid that fits the chip
+//                   settles in one launch, a larger one is launched until nothing changes
+//   k_epic_graph    adjacent-cell pairs, gathered per 64x32 tile in LDS, inserted into fixed-size
+//                   per-seed adjacency rows
+//   k_epic_least    each seed's least edge
 //   k_epic_knn_fit  one wavefront per seed: Dijkstra on the seed graph with the frontier and a
 //                   hash index in LDS, stopped after k settles; FP64 weighted affine fit by
 //                   modified Gram-Schmidt across the wavefront
@@ -31,7 +33,7 @@ namespace {
 
 constexpr int kMaxDeg = 32;          // graph neighbours a seed can hold
 constexpr int kCand = 384;           // candidates one neighbour search can hold (about 210 needed at k 128)
-constexpr int kHash = 512;           // LDS hash slots of one search (power of two, > kCand + kMaxDeg)
+constexpr int kHash = 512;           // LDS hash slots of one search (power of two, > kCand + 64)
 constexpr int kMaxK = 256;           // largest k
 // Relaxation tile: a wavefront holds 64 columns, the outer two of them the neighbouring tiles', and
 // kRRows rows of them, one column's run per lane; kRWaves wavefronts stack up.  The 1242x375 frame
