@@ -138,6 +138,7 @@ __device__ __forceinline__ void chain_level(const PyrChain &A, int f, int bx, in
     __syncthreads();
     uint8_t *dst = A.dst[k1 - 1][f];
     const int64_t dp = A.dst_pitch[k1 - 1];
+    const bool even = (((uintptr_t)dst | (uintptr_t)dp) & 1) == 0; // (a caller's buffer may start anywhere)
     for (int t = tid; t < HO * G; t += kChainThreads) {
         const int y = t / G, q = t - y * G;
         const uint2 *p = reinterpret_cast<const uint2 *>(hs) + 2 * y * G + q;
@@ -160,10 +161,12 @@ __device__ __forceinline__ void chain_level(const PyrChain &A, int f, int bx, in
             const int x = 4 * q + 2 * h, gx = ux + x;
             if (x < kHalo || x >= kHalo + kOwn || gx >= W) continue;
             uint8_t *d = dst + (int64_t)gy * dp + gx;
-            if (gx + 1 < W)
+            if (gx + 1 < W && even) {
                 *reinterpret_cast<uint16_t *>(d) = (uint16_t)o[h];
-            else
-                *d = (uint8_t)o[h];
+            } else {
+                d[0] = (uint8_t)o[h];
+                if (gx + 1 < W) d[1] = (uint8_t)(o[h] >> 8);
+            }
         }
     }
     __syncthreads();
@@ -258,6 +261,7 @@ __device__ __forceinline__ void chain_level_f32(const PyrChain &A, int f, int bx
     __syncthreads();
     uint8_t *dst = A.dst[k1 - 1][f];
     const int64_t dp = A.dst_pitch[k1 - 1];
+    const bool even = (((uintptr_t)dst | (uintptr_t)dp) & 7) == 0;
     for (int t = tid; t < HO * G; t += kChainThreads) {
         const int y = t / G, q = t - y * G;
         const float4 *p = reinterpret_cast<const float4 *>(hs) + 2 * y * G + q;
@@ -274,10 +278,12 @@ __device__ __forceinline__ void chain_level_f32(const PyrChain &A, int f, int bx
             if (x < kHalo || x >= kHalo + kOwn || gx >= W) continue;
             float *o = reinterpret_cast<float *>(dst + (int64_t)gy * dp) + gx;
             const float2 w = h ? make_float2(v.z, v.w) : make_float2(v.x, v.y);
-            if (gx + 1 < W)
+            if (gx + 1 < W && even) {
                 *reinterpret_cast<float2 *>(o) = w;
-            else
-                *o = w.x;
+            } else {
+                o[0] = w.x;
+                if (gx + 1 < W) o[1] = w.y;
+            }
         }
     }
     __syncthreads();

@@ -5,12 +5,15 @@ four borders, rows that start at every byte, and float frames whose first level 
 uint8 levels are whole numbers, bit for bit the oracle's.  A float level's pixel is a sum of 25
 products of positive weights whose sum is 1, with at most eight roundings on its way, at most four
 levels deep: 32 x 2^-24 x 255 < 5e-4."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
 import paper_1901_09971_amd as dgf
+from paper_1901_09971_amd import _lib
 
 pytestmark = pytest.mark.gpu
 
@@ -42,3 +45,22 @@ def test_tiles_and_borders(levels):
 @pytest.mark.parametrize("W,H", [(1024, 1024), (1025, 1024), (2050, 1100)])
 def test_first_level_by_itself(W, H):
     _check((W, H), 4)
+
+
+@pytest.mark.parametrize("dtype,shift", [(_lib.DGF_U8, 1), (_lib.DGF_U8, 3), (_lib.DGF_F32, 4)])
+def test_destination_at_any_alignment(dtype, shift):
+    rng = np.random.default_rng(shift)
+    img = rng.integers(0, 256, size=(71, 133), dtype=np.uint8)
+    t = torch.from_numpy(img).cuda()
+    t = t.float() if dtype == _lib.DGF_F32 else t
+    e = t.element_size()
+    L = _lib.lib()
+    im = _lib.DgfImage(t.data_ptr(), 133, 71, 133 * e, dtype)
+    need = L.dgf_pyramid_layout(133, 71, 5, dtype, None, None)
+    out = []
+    for at in (0, shift):
+        buf = torch.zeros(need + 64, dtype=torch.uint8, device="cuda")
+        assert L.dgf_pyramid(ctypes.byref(im), 5, ctypes.c_void_p(buf.data_ptr() + at), need, None) == 0
+        torch.cuda.synchronize()
+        out.append(buf[at:at + need].cpu().numpy())
+    assert np.array_equal(out[0], out[1])
