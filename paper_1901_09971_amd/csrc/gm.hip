@@ -3,8 +3,8 @@
 // the motions of the points that the coarsest-level pass reports converged, by weighted least
 // squares and then ten Tukey-biweight reweightings.
 //
-// One launch per weighting pass, each a grid of (nblk, npairs) workgroups.  Every workgroup first
-// rebuilds the previous pass's model from the previous pass's partial sums (all workgroups of a pair
+// Pairs of up to 4096 points are fitted by one workgroup in one launch (k_gm_one).  The larger ones
+// take one launch per weighting pass, each a grid of (nblk, npairs) workgroups.  Every workgroup first rebuilds the previous pass's model from the previous pass's partial sums (all workgroups of a pair
 // reduce the same partials in the same order, so they agree bit for bit), then sums its slice of the
 // pair's samples under the weights that model gives.  A last launch of one workgroup per pair turns
 // the final partial sums into the model.
@@ -15,7 +15,7 @@
 // of values a lane carries; every lane solves for the model (no broadcast, no second barrier) and
 // pivots by selection.  12065 points: 119 us for the twelve launches with slices of 2048 points read one
 // by one, full butterflies and one lane solving through indexed rows, 82 with the shorter chain,
-// 68 with slices of 512 (an empty slice: 59).
+// 68 with slices of 512, 63 with the narrow steps of the sums off the LDS pipe.
 //
 // Models and partials are double-buffered by pass parity, so
 // a launch only reads what the launch before it wrote: no atomics and no counters to clear, and the
@@ -36,13 +36,17 @@ static_assert(kNz + 1 == kGmSums, "sum layout");
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 static_assert(kGmMaxBlocks <= kThreads, "one partial per lane");
+constexpr int64_t kGmOne = 4096; // points of a pair that one workgroup fits in one launch
 constexpr int kHold = 4; // samples a lane fetches at a time (slices above 131072 points in all are longer than two)
 
-// v + the value of v in lane ^ M, both lanes of a pair alike.
-template <int M>
-__device__ __forceinline__ double add_xor(double v)
+// v + the value of v in the lane that the DPP control pairs this one with.
+template <int CTRL>
+__device__ __forceinline__ double add_dpp(double v)
 {
-    return v + __shfl_xor(v, M, 64);
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    const uint2 o = {(unsigned)__builtin_amdgcn_mov_dpp((int)u.x, CTRL, 0xF, 0xF, true),
+                     (unsigned)__builtin_amdgcn_mov_dpp((int)u.y, CTRL, 0xF, 0xF, true)};
+    return v + __builtin_bit_cast(double, o);
 }
 
 // One halving step of the wavefront's sum over the lanes M apart: on return the lanes of the lower
@@ -63,11 +67,10 @@ __device__ __forceinline__ double add_split(double a, double b)
     return __builtin_bit_cast(double, uint2{lo[0], hi[0]}) + __builtin_bit_cast(double, uint2{lo[1], hi[1]});
 }
 
-// Sum of v[k] over the workgroup in a fixed order (lane butterflies, then the four wavefronts in
-// turn); after the call every lane's out[k] holds it.  The butterfly's two widest steps halve the
-// number of values a lane carries instead of exchanging all of them, which leaves 4 of the 16
-// (13 and three zeros) for the four narrow steps: 16 exchanges of a double against 78.
-__device__ void block_sum(const double (&v)[kGmSums], double (*red)[16], double (&out)[kGmSums])
+// Sums of v[k] over the wavefront, to one row of 16: the butterfly's two widest steps halve the number of
+// values a lane carries instead of exchanging all of them, which leaves 4 of the 16 (13 and three
+// zeros) for the four narrow steps, inside rows of lanes: 16 exchanges of a double against 78, none through LDS.
+__device__ __forceinline__ void wave_sums(const double (&v)[kGmSums], double (&row)[16])
 {
     double h[8], q[4];
 #pragma unroll
@@ -75,15 +78,22 @@ __device__ void block_sum(const double (&v)[kGmSums], double (*red)[16], double 
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         q[k] = add_split<16>(h[k], h[k + 4]);
-        q[k] = add_xor<8>(q[k]);
-        q[k] = add_xor<4>(q[k]);
-        q[k] = add_xor<2>(q[k]);
-        q[k] = add_xor<1>(q[k]);
+        q[k] = add_dpp<0xB1>(q[k]);  // lane ^ 1
+        q[k] = add_dpp<0x4E>(q[k]);  // lane ^ 2
+        q[k] = add_dpp<0x141>(q[k]); // the other four of eight
+        q[k] = add_dpp<0x140>(q[k]); // the other eight of sixteen
     }
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63;
     if ((lane & 15) == 0)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) red[wave][(lane >> 5) * 8 + ((lane >> 4) & 1) * 4 + k] = q[k];
+        for (int k = 0; k < 4; ++k) row[(lane >> 5) * 8 + ((lane >> 4) & 1) * 4 + k] = q[k];
+}
+
+// Sum of v[k] over the workgroup in a fixed order (lane butterflies, then the four wavefronts in
+// turn); after the call every lane's out[k] holds it.
+__device__ void block_sum(const double (&v)[kGmSums], double (*red)[16], double (&out)[kGmSums])
+{
+    wave_sums(v, red[threadIdx.x >> 6]);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kGmSums; ++k) {
@@ -162,6 +172,111 @@ __device__ __forceinline__ void gm_solve(const double (&S)[kGmSums], double (&A)
     }
 }
 
+// A sample's part in the sums of pass `pass` under the model A (pass 0: weight 1).
+__device__ __forceinline__ void add_sample(float2 p, float2 m, double cx, double cy, double c2, int pass,
+                                           const double (&A)[6], double (&v)[kGmSums])
+{
+    if (!isfinite(m.x) || !isfinite(m.y)) return;
+    const double x = (double)p.x - cx, y = (double)p.y - cy, mu = m.x, mv = m.y;
+    double w = 1.0;
+    if (pass > 0) {
+        const double ex = mu - (A[0] * x + A[1] * y + A[2]);
+        const double ey = mv - (A[3] * x + A[4] * y + A[5]);
+        const double e2 = ex * ex + ey * ey;
+        const double q = 1.0 - e2 / c2;
+        w = e2 < c2 ? q * q : 0.0;
+    }
+    if (!(w > 0.0)) return;
+    const double wx = w * x, wy = w * y;
+    v[kS] += w;
+    v[kSx] += wx;
+    v[kSy] += wy;
+    v[kSxx] += wx * x;
+    v[kSxy] += wx * y;
+    v[kSyy] += wy * y;
+    v[kSu] += w * mu;
+    v[kSxu] += wx * mu;
+    v[kSyu] += wy * mu;
+    v[kSv] += w * mv;
+    v[kSxv] += wx * mv;
+    v[kSyv] += wy * mv;
+    v[kNz] += 1.0;
+}
+
+// The points of a pair and its frame size.
+struct GmPair {
+    int64_t p0, p1;
+    int W, H;
+};
+
+__device__ __forceinline__ GmPair gm_pair(const GmFit &g, int pair)
+{
+    if (!g.pt_off) return {0, g.n, g.W, g.H};
+    const LevelPair &l = g.blv[(size_t)pair * g.L];
+    return {g.pt_off[pair], g.pt_off[pair + 1], l.W, l.H};
+}
+
+// The whole fit of a pair of up to kGmOne points by one workgroup, its samples in registers: a
+// pass is then two barriers and the workgroup's FP64 issue instead of a launch.  Above, that issue
+// costs more than a launch's latency.  The twelve launches against the one: 100 points 59 -> 27 us, 4,000 points
+// 67 -> 43; 8,000 points would take 59 for 62.
+constexpr int kOneThreads = 1024, kOneHold = kGmOne / kOneThreads;
+
+__global__ __launch_bounds__(kOneThreads) void k_gm_one(GmFit g)
+{
+    __shared__ double red[kOneThreads / 64][16];
+    __shared__ double model[6];
+    const GmPair P = gm_pair(g, (int)blockIdx.x);
+    if (P.p1 - P.p0 > kGmOne) return;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const double cx = 0.5 * (P.W - 1), cy = 0.5 * (P.H - 1), c2 = g.c * g.c;
+    float2 hp[kOneHold], hm[kOneHold];
+    uint8_t hs[kOneHold];
+#pragma unroll
+    for (int j = 0; j < kOneHold; ++j) {
+        const int64_t i = P.p0 + t + kOneThreads * j;
+        hs[j] = DGF_ST_CONVERGED + 1;
+        if (i < P.p1) {
+            hp[j] = g.pts[i];
+            hm[j] = g.flow[i];
+            hs[j] = g.status[i];
+        }
+    }
+    double A[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int pass = 0; pass < kGmPasses; ++pass) {
+        double v[kGmSums];
+#pragma unroll
+        for (int k = 0; k < kGmSums; ++k) v[k] = 0.0;
+#pragma unroll
+        for (int j = 0; j < kOneHold; ++j)
+            if (hs[j] == DGF_ST_CONVERGED) add_sample(hp[j], hm[j], cx, cy, c2, pass, A, v);
+        wave_sums(v, red[wave]);
+        __syncthreads();
+        if (wave == 0) {
+            // lane k (mod 16) sums value k over four wavefronts, then the four rows of lanes
+            double x = 0.0;
+#pragma unroll
+            for (int w = 0; w < kOneThreads / 256; ++w) x += red[(lane >> 4) * (kOneThreads / 256) + w][lane & 15];
+            x += __shfl_xor(x, 16, 64);
+            x += __shfl_xor(x, 32, 64);
+            const uint2 u = __builtin_bit_cast(uint2, x);
+            double S[kGmSums];
+#pragma unroll
+            for (int k = 0; k < kGmSums; ++k)
+                S[k] = __builtin_bit_cast(double, uint2{(unsigned)__builtin_amdgcn_readlane((int)u.x, k),
+                                                        (unsigned)__builtin_amdgcn_readlane((int)u.y, k)});
+            gm_solve(S, A);
+            if (lane == 0)
+#pragma unroll
+                for (int k = 0; k < 6; ++k) model[k] = A[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 6; ++k) A[k] = model[k];
+    }
+    if (t < 6) g.models[(size_t)blockIdx.x * 6 + t] = model[t];
+}
+
 // Pass `pass` (0 .. kGmPasses - 1) sums its slice under the weights of the model of pass - 1 (pass
 // 0: weight 1 on every sample); pass kGmPasses only finishes the last model.
 __global__ __launch_bounds__(kThreads) void k_gm_pass(GmFit g, int pass)
@@ -169,14 +284,10 @@ __global__ __launch_bounds__(kThreads) void k_gm_pass(GmFit g, int pass)
     __shared__ double red[2][kWaves][16];
     const int pair = blockIdx.y;
     const int t = threadIdx.x;
-    int64_t p0 = 0, p1 = g.n;
-    int W = g.W, H = g.H;
-    if (g.pt_off) {
-        p0 = g.pt_off[pair];
-        p1 = g.pt_off[pair + 1];
-        W = g.blv[(size_t)pair * g.L].W;
-        H = g.blv[(size_t)pair * g.L].H;
-    }
+    const GmPair P = gm_pair(g, pair);
+    const int64_t p0 = P.p0, p1 = P.p1;
+    const int W = P.W, H = P.H;
+    if (p1 - p0 <= kGmOne) return; // (k_gm_one's)
     const int nb = gm_blocks(p1 - p0); // this pair's workgroups (the grid covers the largest pair)
     if ((int)blockIdx.x >= nb) return;
     const int64_t chunk = (p1 - p0 + nb - 1) / nb;
@@ -228,32 +339,7 @@ __global__ __launch_bounds__(kThreads) void k_gm_pass(GmFit g, int pass)
         if (i0 != b0) fetch(i0);
 #pragma unroll
         for (int j = 0; j < kHold; ++j) {
-            const float2 m = hm[j], p = hp[j];
-            if (hs[j] != DGF_ST_CONVERGED || !isfinite(m.x) || !isfinite(m.y)) continue;
-            const double x = (double)p.x - cx, y = (double)p.y - cy, mu = m.x, mv = m.y;
-            double w = 1.0;
-            if (pass > 0) {
-                const double ex = mu - (A[0] * x + A[1] * y + A[2]);
-                const double ey = mv - (A[3] * x + A[4] * y + A[5]);
-                const double e2 = ex * ex + ey * ey;
-                const double q = 1.0 - e2 / c2;
-                w = e2 < c2 ? q * q : 0.0;
-            }
-            if (!(w > 0.0)) continue;
-            const double wx = w * x, wy = w * y;
-            v[kS] += w;
-            v[kSx] += wx;
-            v[kSy] += wy;
-            v[kSxx] += wx * x;
-            v[kSxy] += wx * y;
-            v[kSyy] += wy * y;
-            v[kSu] += w * mu;
-            v[kSxu] += wx * mu;
-            v[kSyu] += wy * mu;
-            v[kSv] += w * mv;
-            v[kSxv] += wx * mv;
-            v[kSyv] += wy * mv;
-            v[kNz] += 1.0;
+            if (hs[j] == DGF_ST_CONVERGED) add_sample(hp[j], hm[j], cx, cy, c2, pass, A, v);
         }
     }
     double S[kGmSums];
@@ -276,6 +362,13 @@ size_t gm_state_bytes(int npairs, int nblk)
 
 hipError_t launch_gm_fit(const GmFit &g, hipStream_t st)
 {
+    // a pair's form depends on its own point count; either launch leaves the other's pairs alone
+    if (g.npairs > 1 || g.nblk <= gm_blocks(kGmOne)) {
+        hipLaunchKernelGGL(k_gm_one, dim3(g.npairs), dim3(kOneThreads), 0, st, g);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (g.nblk <= gm_blocks(kGmOne)) return hipSuccess; // no larger pair
     for (int pass = 0; pass <= kGmPasses; ++pass) {
         const dim3 grid(pass < kGmPasses ? g.nblk : 1, g.npairs);
         hipLaunchKernelGGL(k_gm_pass, grid, dim3(kThreads), 0, st, g, pass);

@@ -1,4 +1,4 @@
-"""The global-motion fit at the edges of its slices: one slice more or less, a slice longer than the
+"""The global-motion fit at the edges of its forms (one workgroup up to 4096 points) and slices: one slice more or less, a slice longer than the
 lanes hold at a time, and frames whose normal equations are pivoted on each of their rows (wide,
 tall, and so small that the constant row is the largest).
 
@@ -21,7 +21,7 @@ def _corners(A, W, H):
 
 
 @pytest.mark.parametrize("n,W,H", [(511, 1242, 375), (512, 1242, 375), (513, 375, 1242), (1025, 375, 1242),
-                                   (700, 2, 2), (131073, 640, 480), (262145, 480, 640), (300001, 2, 2)])
+                                   (700, 2, 2), (1023, 640, 480), (4096, 375, 1242), (4097, 640, 480), (131073, 640, 480), (262145, 480, 640), (300001, 2, 2)])
 def test_fit_at_slice_edges(n, W, H):
     rng = np.random.default_rng(n)
     pts = np.stack([rng.uniform(0, W - 1, n), rng.uniform(0, H - 1, n)], 1).astype(np.float32)
@@ -44,3 +44,22 @@ def test_fit_at_slice_edges(n, W, H):
         err = np.abs(_corners(g.cpu().numpy(), W, H) - want).max() / (1.0 + np.abs(want).max())
         print(f"n={n} {W}x{H} rel={err:.2e}", flush=True)
         assert err <= 1e-9
+
+
+def test_plan_with_pairs_on_both_sides():
+    rng = np.random.default_rng(3)
+    pairs = []
+    for W, H, stride in ((320, 240, 5), (400, 320, 5), (331, 203, 3), (90, 70, 5)):
+        I0 = rng.integers(0, 256, (H // 4 + 2, W // 4 + 2)).astype(np.uint8).repeat(4, 0).repeat(4, 1)[:H + 3, :W + 2]
+        a, b = torch.from_numpy(I0[:H, :W].copy()).cuda(), torch.from_numpy(I0[3:H + 3, 2:W + 2].copy()).cuda()
+        pairs.append((a, b, 9, stride))
+    opts = dgf.TrackOpts(global_motion=True)
+    plan = dgf.Batch(pairs, 3, 9, 10, opts)
+    sizes = np.diff(plan.offsets)
+    assert sizes.min() < 512 and (sizes <= 4096).any() and (sizes > 4096).any()
+    pts, flow, status = plan.run()
+    for k, (a, b, w, stride) in enumerate(pairs):
+        lo, hi = plan.offsets[k], plan.offsets[k + 1]
+        f, st = dgf.track(a, b, dgf.detect(a, w, stride), 3, 9, 10, opts=opts)
+        assert torch.equal(st, status[lo:hi])
+        assert torch.equal(torch.nan_to_num(f, nan=-1e9), torch.nan_to_num(flow[lo:hi], nan=-1e9)), k
