@@ -300,7 +300,7 @@ __device__ __forceinline__ void adjoint_point(const AdjParams &A, const AdjPair 
     // psi(r) / r for the test below.  An idle lane's pixels are run 0's (see above): a residual of zero
     // among them would give 0 / 0 where ps and dps are cleared outside the support, so they weigh 1.
     auto weight = [&](int k) {
-        return dps[k] == 1.f || !in_support(k) ? 1.f : ps[k] * __builtin_amdgcn_rcpf(res[k]);
+        return dps[k] == 1.f || !in_support(k) ? 1.f : ps[k] / res[k];
     };
     // the least-squares equations' psi
     auto least_squares = [&]() {
