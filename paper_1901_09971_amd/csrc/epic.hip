@@ -172,7 +172,7 @@ __global__ void k_epic_seed(const float *pts, const float *flow, const uint8_t *
 //   Fast: distances below kFar, whose keys as bit patterns are positive doubles, so that one
 //         v_min_f64 takes the lesser of two (denormals are kept in double precision).  No key is
 //         kFar in the distance half; kFar plus any step stays below the doubles' infinities.
-//   else: any distance below kDistCap, by 64-bit integer comparisons; kNoKey plus any step stays kNoKey.
+//   else: any distance up to kDistCap, by 64-bit integer comparisons; a sum beyond that is no key.
 constexpr uint32_t kFar = 0x3F000000u;
 
 enum : uint32_t { kDone = 1u, kLeave = 2u };
@@ -212,10 +212,11 @@ __device__ __forceinline__ uint64_t key_relax(uint64_t mine, uint64_t from, uint
         asm("v_min_f64 %0, %0, %1" : "+v"(a) : "v"(v));
         return __builtin_bit_cast(uint64_t, a);
     } else {
-        uint32_t d = hi + c;
-        d = d < hi ? 0xFFFFFFFFu : d;
+        // a sum at or beyond all ones is no distance (the wavefront's end lanes shift in zeros, whose sum with
+        // a wall is all ones exactly)
+        const uint32_t d = hi + c;
         const uint64_t v = ((uint64_t)d << 32) | lo;
-        return v < mine ? v : mine;
+        return d >= hi && d != 0xFFFFFFFFu && v < mine ? v : mine;
     }
 }
 
