@@ -52,7 +52,6 @@ constexpr int kStartPolls = 256;     // polls a resident grid waits for tiles th
 constexpr int kChunk = 4;            // relaxation launches between two convergence checks, and sets of their counters
 constexpr int kMaxRelaxLaunches = 1 << 14;
 constexpr int kDefaultAsyncRelax = 32; // dgf_epic_async's relaxation launches when given 0
-constexpr int kRestBlocks = 128;     // workgroups of the launches after a resident grid's second
 constexpr uint64_t kNoKey = ~0ull;
 constexpr uint64_t kDistCap = 0xFFFFFFFEull;
 constexpr int kMaxEdge = 510;        // largest edge-map value
@@ -258,19 +257,18 @@ __device__ __forceinline__ uint64_t key_shift(uint64_t k)
 // zero the distances are already at the fixed point and the launch returns at once, with nothing
 // changed (so a fixed number of launches can be enqueued without reading anything back).  Each launch
 // clears the counters of the launch after the next, `next`, which nobody reads or writes meanwhile.
-// Without `wait` a workgroup takes several tiles in turn when the grid is smaller than their number.
 template <bool FAST>
 __global__ __launch_bounds__(kRelaxThreads, 5) void k_epic_relax(int W, int H, int kappa, uint64_t *keys,
                                                                  const uint16_t *E, RelaxCounters now, int wait,
-                                                                 RelaxCounters prev, RelaxCounters next, int tiles_x,
-                                                                 int tiles)
+                                                                 RelaxCounters prev, RelaxCounters next, int tiles_x)
 {
     constexpr uint32_t wall = kWall<FAST>;
     constexpr int R = kRRows;
     uint32_t *const mail = now.mail, *const state = now.state;
+    const int me = (int)blockIdx.x, tiles = (int)gridDim.x;
     if (threadIdx.x == 0) {
-        for (int t = (int)blockIdx.x; t < tiles; t += (int)gridDim.x) next.mail[t] = next.state[t] = 0u;
-        if (blockIdx.x == 0) *next.changed = *next.open = *next.done = 0u;
+        next.mail[me] = next.state[me] = 0u;
+        if (me == 0) *next.changed = *next.open = *next.done = 0u;
     }
     // (the same values in every block: an earlier kernel wrote them)
     if (prev.changed && (*prev.changed == 0u || *prev.open == 0u)) return;
@@ -278,7 +276,6 @@ __global__ __launch_bounds__(kRelaxThreads, 5) void k_epic_relax(int W, int H, i
     __shared__ uint64_t rows[2 * kRWaves + 2][64];
     __shared__ uint32_t flags[2][kRWaves];
     __shared__ uint32_t sides, poll;
-    for (int me = (int)blockIdx.x; me < tiles; me += (int)gridDim.x) {
     const int tile_y = me / tiles_x, tile_x = me - tile_y * tiles_x;
     const int nbr_tile[4] = {tile_x > 0 ? me - 1 : -1, tile_x + 1 < tiles_x ? me + 1 : -1,
                              tile_y > 0 ? me - tiles_x : -1, me + tiles_x < tiles ? me + tiles_x : -1};
@@ -485,7 +482,6 @@ __global__ __launch_bounds__(kRelaxThreads, 5) void k_epic_relax(int W, int H, i
         if (!settled) atomicAdd(now.open, 1u);
         if (wrote) atomicAdd(now.changed, 1u);
     }
-    } // tiles
 }
 
 // Insert (or lower) the edge s -> t of length w into s's adjacency row: a slot holds
@@ -1162,20 +1158,19 @@ int epic_run(const dgf_image *I0, const float *points, const float *flow, const 
             return DGF_ERR_HIP;
         const int wait = ntiles <= (int64_t)cus * per_cu ? 1 : 0;
         const int limit = sync ? kMaxRelaxLaunches : max_relax;
-        // a grid that fits the chip settles in its first launch, unless other work keeps it from
-        // being resident, and the second says so; the launches after that mostly return at once, and
-        // a few workgroups do so sooner than one for each tile (2.5 against 5 us on 1,088 tiles)
-        auto blocks = [&](int launch) {
-            return dim3((unsigned)(wait && launch >= 2 ? std::min<int64_t>(ntiles, kRestBlocks) : ntiles));
-        };
+        // a grid that fits the chip settles in its first launch and the second says so; where other work
+        // keeps it from being resident for a while, any later launch may be the one that settles it, so all
+        // of them wait.  (With 128 workgroups that do not wait from the third launch on, one returns in 2.5 us
+        // instead of 5 on 1,088 tiles, but 4 calls side by side on 1400x700 frames of one seed could end unsettled
+        // after 32 launches.)
         int done = 0; // launches so far; launch j uses counter set j mod kChunk
         auto relax = [&](int launches) {
             for (const int end = done + std::min(launches, limit - done); done < end; ++done) {
                 const RelaxCounters prev = done > 0 ? relax_counters(ws, done - 1, ntiles) : RelaxCounters{};
-                hipLaunchKernelGGL(fast ? k_epic_relax<true> : k_epic_relax<false>, blocks(done), dim3(kRelaxThreads), 0, st,
-                                   W, H, o.kappa, ws.keys, (const uint16_t *)ws.E, relax_counters(ws, done, ntiles),
-                                   wait && done < 2 ? 1 : 0, prev, relax_counters(ws, done + 2, ntiles), (int)tiles.x,
-                                   (int)ntiles);
+                hipLaunchKernelGGL(fast ? k_epic_relax<true> : k_epic_relax<false>, dim3((unsigned)ntiles), dim3(kRelaxThreads),
+                                   0, st, W, H, o.kappa, ws.keys, (const uint16_t *)ws.E,
+                                   relax_counters(ws, done, ntiles), wait, prev, relax_counters(ws, done + 2, ntiles),
+                                   (int)tiles.x);
                 if (hipGetLastError() != hipSuccess) return false;
             }
             return true;

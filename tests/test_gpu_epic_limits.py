@@ -1,5 +1,6 @@
-"""The dense interpolation at the limits of its parameters: no seed at all with both key forms of the
-relaxation (distances beyond the fast form's range come with a large kappa on a large frame)."""
+"""The dense interpolation at the limits of its parameters and surroundings: no seed at all with both key
+forms of the relaxation (distances beyond the fast form's range come with a large kappa on a large
+frame); calls side by side on several streams, whose grids are not resident at once."""
 import numpy as np
 import pytest
 import torch
@@ -27,3 +28,28 @@ def test_no_seed(W, H, kappa, run):
     assert torch.all(g["labels"] == -1) and torch.all(g["dist"] == -1)  # (uint32 0xFFFFFFFF)
     assert torch.all(torch.isnan(out[0])) and torch.all(torch.isnan(g["model"]))
     assert torch.all(g["nbr"] == -1) and torch.all(g["nbr_dist"] == -1)
+
+
+@pytest.mark.parametrize("W,H", [(1400, 700), (1600, 900), (2048, 1024)])
+def test_async_calls_side_by_side(W, H):
+    """One seed in a corner, so that its distances cross every tile, on four streams at a time: the
+    relaxation grids keep each other from being resident, and tiles leave to make room for those that
+    have not started.  Every call settles within the default number of launches all the same."""
+    rng = np.random.default_rng(W)
+    I0 = torch.from_numpy(rng.integers(0, 256, (H, W)).astype(np.uint8)).cuda()
+    P = torch.tensor([[W - 3.0, H - 3.0]], device="cuda")
+    F, st = torch.tensor([[0.5, -1.0]], device="cuda"), torch.zeros(1, dtype=torch.uint8, device="cuda")
+    ref, want = dgf.epic(I0, P, F, st, return_aux=True)
+    streams, calls = [torch.cuda.Stream() for _ in range(4)], 8
+    torch.cuda.synchronize()
+    out = []
+    for _ in range(calls):
+        for s in streams:
+            with torch.cuda.stream(s):
+                out.append(dgf.epic_async(I0, P, F, st, return_aux=True))
+    torch.cuda.synchronize()
+    statuses = [int(status.item()) for _, status, _ in out]
+    print(f"{W}x{H}: {sum(s != 0 for s in statuses)} of {len(statuses)} unsettled", flush=True)
+    assert not any(statuses)
+    for dense, _, aux in out:
+        assert torch.equal(dense, ref) and torch.equal(aux["dist"], want["dist"])
