@@ -501,8 +501,10 @@ int dgf_epic(const dgf_image *I0, const float *points, const float *flow, const 
  * host: the same computation and outputs, enqueued on `stream` with a fixed number of geodesic
  * relaxation launches, max_relax (0 = 32; at most 16,384).  A launch after one that changed
  * nothing returns at once, so launches beyond the fixed point cost a few microseconds each.
- * Frames up to about 2048 x 1024 settle in the first (all tiles on the chip at once); larger ones, or a
- * chip shared with other work, take more (dgf_epic launches as many as the frame needs).
+ * Frames up to about 2048 x 1024 reach it in the first (all tiles on the chip at once); larger ones, or a
+ * chip shared with other work, take more (dgf_epic launches as many as the frame needs).  Done
+ * means that the last launch changed nothing, so max_relax is at least one more than the frame
+ * takes: with max_relax = 1 the status is 1 wherever that launch changed a distance.
  * status_out (device uint32, 4-byte aligned) is written by the last kernel of the call: 0 done;
  * 1 the relaxation had not reached its fixed point after max_relax launches (the outputs are not
  * written: run again with more launches); 2 a capacity limit (DGF_ERR_CAPACITY of dgf_epic, with
