@@ -48,6 +48,7 @@ constexpr int kExchange = 8;         // rounds between two halo exchanges
 constexpr int kMaxRounds = 2048;     // rounds per tile and launch
 constexpr int kMaxPolls = 4096;      // halo polls of a still tile per launch
 constexpr int kPollSleep = 2;        // 64-cycle units between two polls
+constexpr int kLinger = 32;          // halo polls of a still tile per launch of a grid that does not fit the chip
 constexpr int kStartPolls = 256;     // polls a resident grid waits for tiles that have not started
 constexpr int kChunk = 4;            // relaxation launches between two convergence checks, and sets of their counters
 constexpr int kMaxRelaxLaunches = 1 << 14;
@@ -252,6 +253,10 @@ __device__ __forceinline__ uint64_t key_shift(uint64_t k)
 // launch that works and the one that confirms; 2048x1024 (1,088 tiles): 624 -> 324 us of relaxation
 // over 32 launches, 160 of them in the working one.  The form before kept 32x64 tiles in LDS, four pixels a lane, at about 28
 // instructions and 5 LDS accesses a pixel and iteration, one column or row per iteration.
+// Without `wait` a still tile looks for mail kLinger times before it leaves, so that a front that comes
+// down or up the rows of tiles on the chip together crosses more than one of them a launch: seeds along the
+// lower edge of 8192x700 reach every pixel in 16 launches (33 without, 8 polls 29, 128 polls 9), and the
+// whole call takes 1,627 us on 4096x2160, 137,459 seeds (1,940 without, 8 polls 1,760, 128 polls 1,893).
 // The launch counts the tiles that changed anything and those that left before they saw the whole
 // grid settled.  prev (nullable) is the counters of the launch before: when either of its counts is
 // zero the distances are already at the fixed point and the launch returns at once, with nothing
@@ -453,9 +458,9 @@ __global__ __launch_bounds__(kRelaxThreads, 5) void k_epic_relax(int W, int H, i
             const uint32_t p = poll;
             resume = (p & 1u) != 0u;
             settled = p == 2u * kDone;
-            if (p || !wait) break;
+            if (p || (!wait && polls >= kLinger)) break;
             ++polls;
-            if (me == 0) {
+            if (wait && me == 0) {
                 const int all = all_settled();
                 settled = all == 1;
                 const bool leave = settled || (all == 2 && polls >= kStartPolls);

@@ -1,6 +1,7 @@
 """The dense interpolation at the limits of its parameters and surroundings: no seed at all with both key
 forms of the relaxation (distances beyond the fast form's range come with a large kappa on a large
-frame); calls side by side on several streams, whose grids are not resident at once."""
+frame); calls side by side on several streams, whose grids are not resident at once; a frame of more
+tiles than the chip holds whose distances cross all its rows of tiles."""
 import numpy as np
 import pytest
 import torch
@@ -53,3 +54,18 @@ def test_async_calls_side_by_side(W, H):
     assert not any(statuses)
     for dense, _, aux in out:
         assert torch.equal(dense, ref) and torch.equal(aux["dist"], want["dist"])
+
+
+@pytest.mark.parametrize("edge", ["lower", "upper"])
+def test_async_default_launches_cross_a_wide_frame(edge):
+    W, H = 8192, 740
+    rng = np.random.default_rng(5)
+    I0 = torch.from_numpy(rng.integers(0, 256, (H, W)).astype(np.uint8)).cuda()
+    x = torch.arange(4.0, W - 4, 40, device="cuda")
+    P = torch.stack([x, torch.full_like(x, H - 3.0 if edge == "lower" else 2.0)], 1).contiguous()
+    F, st = torch.ones_like(P), torch.zeros(len(x), dtype=torch.uint8, device="cuda")
+    _, want = dgf.epic(I0, P, F, st, return_aux=True)
+    _, status, aux = dgf.epic_async(I0, P, F, st, return_aux=True)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    assert torch.equal(aux["labels"], want["labels"]) and torch.equal(aux["dist"], want["dist"])
