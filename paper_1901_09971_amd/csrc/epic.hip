@@ -644,7 +644,7 @@ struct EpicFit {
     const uint64_t *keys;
     EpicWs ws;
     int64_t n;
-    int W, H, k, h;
+    int W, H, k, h, kappa;
     uint32_t dmax;
     int32_t *nbr;
     uint32_t *nbr_dist;
@@ -681,11 +681,18 @@ __device__ __forceinline__ double wave_sum_f64(double v)
 
 __device__ __forceinline__ int hash_slot(int32_t t) { return (int)(((uint32_t)t * 2654435761u) >> 23); }
 
-// A least edge of up to 16 bits in seven, rounded down: 4 bits of exponent above 3 of mantissa (0: below 2).
-__device__ __forceinline__ uint32_t least_code(uint32_t l)
+// A least edge in seven bits, rounded down: 4 bits of exponent, from that of kappa on (no edge is shorter),
+// above 3 of mantissa.  kb: the exponent of kappa, at most 20; edges beyond the range take its end, which
+// stays below 2^29.
+__device__ __forceinline__ uint32_t least_code(uint32_t l, uint32_t kb)
 {
-    const uint32_t e = 31u - (uint32_t)__builtin_clz(l | 1u);
-    return e == 0u ? 0u : e << 3 | (((l << 3) >> e) & 7u);
+    const uint32_t z = (uint32_t)__builtin_clz(l);
+    return min((31u - z - kb) << 3 | (((l << z) >> 28) & 7u), min(15u, 28u - kb) << 3 | 7u);
+}
+
+__device__ __forceinline__ uint32_t least_bound(uint32_t code, uint32_t kb)
+{
+    return ((8u | (code & 7u)) << ((code >> 3) + kb)) >> 3;
 }
 
 // One wavefront per seed s: its k nearest seeds on the seed graph in increasing (distance, index)
@@ -741,22 +748,18 @@ __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
             const int h = hash_slot((int32_t)s);
             hkey[h] = (int32_t)s;
             hval[h] = 0;
-            chash[0] = (uint16_t)h; // (no least edge: alone in its batch whatever T is)
+            chash[0] = (uint16_t)h; // (the code of the shortest edge there can be: alone in its batch)
             cdist[0] = 0u;
         }
-        // a least edge beyond dmax bounds no more than dmax does, so 16 bits of dmax's scale hold it (and
-        // seven its leading ones)
-        const int shift = max(0, 16 - __builtin_clz(F.dmax | 1u));
-        const uint32_t least_cap = min(F.dmax >> shift, 0xFFFFu);
+        const uint32_t kb = 31u - (uint32_t)__builtin_clz((uint32_t)F.kappa);
         int m = 1, first = 0;  // candidates, and the first group of 64 that are not all settled (its slot)
         uint32_t settled = 0u; // nodes below this distance are settled
         __syncthreads();
         for (;;) {
-            // T (distances and least edges are at most dmax <= 2^30, so sums fit)
+            // T (distances are at most dmax <= 2^30 and bounds below 2^29, so sums fit)
             uint32_t T = 0xFFFFFFFFu;
             for (int base = first; base < m; base += 64) {
-                const uint32_t d = cdist[base + li], code = (uint32_t)chash[base + li] >> 9;
-                const uint32_t least = code ? (((8u | (code & 7u)) << (code >> 3)) >> 3) << shift : 1u;
+                const uint32_t d = cdist[base + li], least = least_bound((uint32_t)chash[base + li] >> 9, kb);
                 if (d - settled < 0xFFFFFFFFu - settled) T = min(T, d + least); // settled <= d < all ones
             }
             T = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_min_u32(T));
@@ -822,7 +825,7 @@ __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
             int queued = 0;
             auto insert = [&]() {
                 const bool ok = li < queued;
-                uint32_t least = 0u;
+                uint32_t least = 1u;
                 if (ok) least = least_edge(F.ws, qt); // in flight during the probing
                 // find or claim the node's place (the table is never full: at most kCand + 64 of kHash)
                 int hs = hash_slot(qt);
@@ -845,7 +848,7 @@ __global__ __launch_bounds__(64) void k_epic_knn_fit(EpicFit F)
                 if (is_new) {
                     const int slot = m + before(nbm);
                     hval[hs] = (uint16_t)slot;
-                    chash[slot] = (uint16_t)(hs | least_code(min(least >> shift, least_cap)) << 9);
+                    chash[slot] = (uint16_t)(hs | least_code(least, kb) << 9);
                 }
                 m += total;
                 __syncthreads();
@@ -1124,6 +1127,7 @@ int epic_run(const dgf_image *I0, const float *points, const float *flow, const 
             F.H = H;
             F.k = o.k;
             F.h = o.half_dist;
+            F.kappa = o.kappa;
             F.dmax = (uint32_t)(64u * (uint32_t)o.half_dist);
             F.nbr = nbr;
             F.nbr_dist = nbr_dist;

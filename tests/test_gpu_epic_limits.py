@@ -1,12 +1,15 @@
 """The dense interpolation at the limits of its parameters and surroundings: no seed at all with both key
 forms of the relaxation (distances beyond the fast form's range come with a large kappa on a large
 frame); calls side by side on several streams, whose grids are not resident at once; a frame of more
-tiles than the chip holds whose distances cross all its rows of tiles."""
+tiles than the chip holds whose distances cross all its rows of tiles; half-distances and step costs
+far from the defaults, whose neighbour searches take no longer than the defaults'."""
 import numpy as np
 import pytest
 import torch
 
 import paper_1901_09971_amd as dgf
+from paper_1901_09971_amd import synth
+from test_gpu_epic import _run_both
 
 pytestmark = pytest.mark.gpu
 
@@ -69,3 +72,42 @@ def test_async_default_launches_cross_a_wide_frame(edge):
     torch.cuda.synchronize()
     assert int(status.item()) == 0
     assert torch.equal(aux["labels"], want["labels"]) and torch.equal(aux["dist"], want["dist"])
+
+
+@pytest.mark.parametrize("k,kappa,h,n", [(128, 8, 1 << 20, 900), (64, 1, 1 << 24, 900), (32, 1 << 14, 1 << 20, 400),
+                                         (16, 1 << 20, 1 << 24, 60), (40, 7, 1 << 12, 12), (128, 65535, 1 << 18, 900)])
+def test_large_half_distances(k, kappa, h, n):
+    # few seeds: edges beyond the range that bounds the batches; many: ordinary ones
+    rng = np.random.default_rng(k + n)
+    W, H = 190, 120
+    I0 = (rng.integers(0, 40, (H, W)) + np.where(np.arange(W)[None, :] > 90, 100, 0)).astype(np.uint8)
+    P = np.stack([rng.uniform(0, W - 1, n), rng.uniform(0, H - 1, n)], 1)
+    st = (rng.uniform(size=n) < 0.1).astype(np.uint8)
+    _run_both(I0, P, rng.normal(size=(n, 2)), st, dgf.EpicOpts(k=k, kappa=kappa, half_dist=h))
+
+
+def test_large_half_distance_takes_no_longer():
+    """The neighbours and the size of the searches are about those of the default half-distance, so the
+    time is too (0.97 to 1.05 of it over all half-distances; searches that settle one node a batch took 2.9
+    times as long)."""
+    rng = np.random.default_rng(3)
+    I0 = torch.from_numpy(np.clip(np.rint(synth.smoothed_noise(rng, 640, 480, 2.0)), 0, 255).astype(np.uint8)).cuda()
+    P = dgf.detect(I0, 9, 5)
+    F, st = torch.ones_like(P), torch.zeros(len(P), dtype=torch.uint8, device="cuda")
+
+    def ms(h):
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                dgf.epic_async(I0, P, F, st, opts=dgf.EpicOpts(half_dist=h))
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    ms(64)
+    base, far = ms(64), ms(1 << 20)
+    print(f"half-distance 2^20 takes {far / base:.2f} of 64", flush=True)
+    assert far < 1.7 * base
