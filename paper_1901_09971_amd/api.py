@@ -37,9 +37,19 @@ class TrackOpts:
 # A training step makes four calls of about 12 us of host time each and the GPU waits for them, so the
 # marshalling is kept short: the raw stream (0.3 us) instead of a Stream object (2.8 us), and plain
 # integers where a pointer argument takes them.
+def _raw_stream_getter():
+    """device index -> handle of its current stream; PyTorch's own short route is a private name, so the
+    Stream object stays the way where it is missing."""
+    short = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return short or (lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
+_raw_stream = _raw_stream_getter()
+
+
 def _stream() -> int:
     """The current stream's handle (0: the default stream)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _image(t: torch.Tensor, name: str) -> DgfImage:
