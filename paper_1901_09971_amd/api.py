@@ -279,9 +279,11 @@ def track_backward(I0: torch.Tensor, I1: torch.Tensor, points: torch.Tensor, sup
         if illum.shape != (n, 2) or illum.dtype != torch.float32:
             raise ValueError("illum: expected a float32 [n, 2] tensor")
         illum = illum.contiguous()
-    check(lib().dgf_track_backward(ctypes.byref(a), ctypes.byref(b), _ptr(points.contiguous()), n, support,
-                                   ctypes.byref(o), _ptr(flow.contiguous()), _ptr(status.contiguous()), _ptr(dflow),
-                                   _ptr(dI0), _ptr(dI1), _ptr(dpoints), _ptr(illum), _stream()), "dgf_track_backward")
+    # (named: a copy that nothing holds gives its memory to the next one before the call is made)
+    points, flow, status = points.contiguous(), flow.contiguous(), status.contiguous()
+    check(lib().dgf_track_backward(ctypes.byref(a), ctypes.byref(b), _ptr(points), n, support, ctypes.byref(o),
+                                   _ptr(flow), _ptr(status), _ptr(dflow), _ptr(dI0), _ptr(dI1), _ptr(dpoints),
+                                   _ptr(illum), _stream()), "dgf_track_backward")
 
 
 def detect_backward(frame: torch.Tensor, window: int, stride: int, sel: torch.Tensor, dpoints: torch.Tensor,
@@ -292,9 +294,9 @@ def detect_backward(frame: torch.Tensor, window: int, stride: int, sel: torch.Te
     n = int(lib().dgf_detect_count(a.width, a.height, window, stride))
     if dI0.dtype != torch.float32 or dI0.dim() != 2 or dI0.shape != frame.shape or dI0.stride(1) != 1:
         raise ValueError("dI0: expected a float32 [H, W] tensor with unit column stride")
-    dpoints = dpoints.contiguous().to(torch.float32)
-    check(lib().dgf_detect_backward(ctypes.byref(a), window, stride, _ptr(sel.contiguous()), _ptr(dpoints), n,
-                                    _ptr(dI0), dI0.stride(0), _stream()), "dgf_detect_backward")
+    dpoints, sel = dpoints.contiguous().to(torch.float32), sel.contiguous()
+    check(lib().dgf_detect_backward(ctypes.byref(a), window, stride, _ptr(sel), _ptr(dpoints), n, _ptr(dI0),
+                                    dI0.stride(0), _stream()), "dgf_detect_backward")
 
 
 class DetectFn(torch.autograd.Function):
@@ -398,10 +400,11 @@ def _epic_buffers(frame, points, flow, status, opts, return_aux, workspace, dens
                    nbr_dist=torch.empty((n, o.k), dtype=torch.int32, device=dev),  # uint32 bits
                    model=torch.empty((n, 6), dtype=torch.float32, device=dev))
     g = (lambda key: _ptr(aux[key])) if aux else (lambda key: None)
-    args = (ctypes.byref(a), _ptr(points.contiguous()), _ptr(flow.contiguous()), _ptr(status.contiguous()), n,
-            ctypes.byref(o.to_c()), _ptr(workspace), workspace.numel(), _ptr(dense), 2 * W, g("labels"), g("dist"),
-            g("nbr"), g("nbr_dist"), g("model"))
-    return args, dense, aux
+    # (held by the caller until its call is made)
+    keep = (points.contiguous(), flow.contiguous(), status.contiguous(), workspace)
+    args = (ctypes.byref(a), _ptr(keep[0]), _ptr(keep[1]), _ptr(keep[2]), n, ctypes.byref(o.to_c()), _ptr(workspace),
+            workspace.numel(), _ptr(dense), 2 * W, g("labels"), g("dist"), g("nbr"), g("nbr_dist"), g("model"))
+    return args, dense, aux, keep
 
 
 def epic(frame: torch.Tensor, points: torch.Tensor, flow: torch.Tensor, status: torch.Tensor,
@@ -409,7 +412,7 @@ def epic(frame: torch.Tensor, points: torch.Tensor, flow: torch.Tensor, status: 
     """Dense flow float32 [H, W, 2] of the uint8 ``frame`` interpolated from the tracked ``points``
     (float32 [n, 2]) with their ``flow`` and ``status`` (dgf_epic).  With ``return_aux`` also a dict
     of labels and dist [H, W], nbr and nbr_dist [n, k] and model [n, 6].  Synchronises the stream."""
-    args, dense, aux = _epic_buffers(frame, points, flow, status, opts, return_aux, workspace, None)
+    args, dense, aux, _keep = _epic_buffers(frame, points, flow, status, opts, return_aux, workspace, None)
     check(lib().dgf_epic(*args, _stream()), "dgf_epic")
     if return_aux:
         return dense, aux
@@ -424,7 +427,7 @@ def epic_async(frame: torch.Tensor, points: torch.Tensor, flow: torch.Tensor, st
     graph: ``max_relax`` geodesic relaxation launches (0 = the library default).  Returns
     (dense, status_out[, aux]); status_out, an int32 [1] device tensor, holds 0 when done, 1 when
     the relaxation needed more launches (nothing written), 2 on a capacity limit."""
-    args, dense, aux = _epic_buffers(frame, points, flow, status, opts, return_aux, workspace, dense)
+    args, dense, aux, _keep = _epic_buffers(frame, points, flow, status, opts, return_aux, workspace, dense)
     if status_out is None:
         status_out = torch.empty(1, dtype=torch.int32, device=frame.device)
     elif status_out.dtype != torch.int32 or status_out.numel() < 1 or not status_out.is_cuda:
