@@ -16,8 +16,15 @@ namespace dgf {
 // pair, stride 2, support 21, 262,382 converged points: 1.68 ms against 0.64 ms here, of which
 // 0.40 ms is VALU issue, 940 instructions per point); 16 x 8 points per workgroup leave about 110.
 // Eight wavefronts and at most 78 KB keep two workgroups on a CU, so one's ends overlap the other.
+// Where few of a tile's points converged, clearing and emptying its LDS tiles costs more than their
+// atomics: up to kAdjFew go to the maps directly (four 1242x375 pairs, stride 5, support 21, 73,112
+// points of which 2 % converged: 35 us, 48 through the tiles, 36 with a wavefront per point; 20 %:
+// 90, 86 and 130).  A wavefront takes up to eight points one after the other, so a small block of
+// converged points in a plan of others is the one pattern that a wavefront per point does faster (two
+// 520x400 pairs, stride 2, support 9, one ninth of the points in a corner: 36 us against 45).
 constexpr int kAdjWaves = 8;
 constexpr int kAdjPoints = 128; // most points of a tile
+constexpr int kAdjFew = 6;      // so few converged points of a tile go to device memory directly
 
 template <typename PixT, int S, bool IM>
 __global__ __launch_bounds__(64 * kAdjWaves, 4) void k_track_adjoint_tiled(AdjParams A)
@@ -42,14 +49,17 @@ __global__ __launch_bounds__(64 * kAdjWaves, 4) void k_track_adjoint_tiled(AdjPa
     const int np = (int)(A.pt_off[lo + 1] - p0);
     const int tile = (int)((int64_t)blockIdx.x - Pr.tile_first);
     const int tiles_x = (Pr.nx + Pr.tx - 1) / Pr.tx;
-    const int by = tile / tiles_x, bx = tile - by * tiles_x;
+    // every row of tiles starts at a column of its own: the dispatcher deals workgroups out in a fixed turn
+    // (8 dies, 4 engines each), and with 32 tiles a row those of a frame's left half would all go to the
+    // same engines (two 520x400 pairs, stride 2, support 9, illumination model, left half converged: 196 us,
+    // 148 now)
+    const int by = tile / tiles_x, turn = (int)(((uint32_t)by * 2654435761u >> 8) % (uint32_t)tiles_x);
+    const int at = tile - by * tiles_x + turn, bx = at < tiles_x ? at : at - tiles_x;
     if (t == 0) {
         count = lock[0] = lock[1] = 0;
         minx = 0x7fffffff;
         miny = 0x7fffffff;
     }
-    float *tile0 = smem + kAdjWaves * AdjSplit<S>::floats, *tile1 = tile0 + Pr.w0 * Pr.h0;
-    for (int c = t; c < Pr.w0 * Pr.h0 + Pr.w1 * Pr.h1; c += 64 * kAdjWaves) tile0[c] = 0.f;
     __syncthreads();
     // the tile's converged points and their patch origins
     if (t < Pr.tx * Pr.ty) {
@@ -69,6 +79,10 @@ __global__ __launch_bounds__(64 * kAdjWaves, 4) void k_track_adjoint_tiled(AdjPa
     __syncthreads();
     const int n = count;
     if (n == 0) return;
+    const bool tiled = n > kAdjFew;
+    float *tile0 = smem + kAdjWaves * AdjSplit<S>::floats, *tile1 = tile0 + Pr.w0 * Pr.h0;
+    if (tiled)
+        for (int c = t; c < Pr.w0 * Pr.h0 + Pr.w1 * Pr.h1; c += 64 * kAdjWaves) tile0[c] = 0.f;
     if (t < n) { // median by rank
         const int x = lx1[t], y = ly1[t];
         int bxr = 0, byr = 0;
@@ -101,10 +115,11 @@ __global__ __launch_bounds__(64 * kAdjWaves, 4) void k_track_adjoint_tiled(AdjPa
         auto fits = [](int o, int t0, int w, int n0) {
             return n0 >= w && o >= t0 && (uint32_t)o - (uint32_t)t0 <= (uint32_t)(n0 - w);
         };
-        K.fit0 = fits(pl.ox0, K.tx0, W0, Pr.w0) && fits(pl.oy0, K.ty0, W0, Pr.h0);
-        K.fit1 = fits(pl.ox1, K.tx1, W1, Pr.w1) && fits(pl.oy1, K.ty1, W1, Pr.h1);
+        K.fit0 = tiled && fits(pl.ox0, K.tx0, W0, Pr.w0) && fits(pl.oy0, K.ty0, W0, Pr.h0);
+        K.fit1 = tiled && fits(pl.ox1, K.tx1, W1, Pr.w1) && fits(pl.oy1, K.ty1, W1, Pr.h1);
         adjoint_point<PixT, S, IM, false>(A, Pr, i, pl, own, li, K);
     }
+    if (!tiled) return; // (the same for every wavefront)
     __syncthreads();
     // the tiles' cells at their clamped image positions, one row per wavefront and step
     const AdjPair M = *map_of(K.pair);
@@ -148,7 +163,9 @@ hipError_t launch_tiled(const AdjParams &A, unsigned tiles, size_t lds, hipStrea
 // Tile shape for a pair of nx x ny grid points of a plan of n points: the largest of a few shapes whose
 // two LDS tiles let two workgroups share a CU and that leaves the chip at least kMinTiles workgroups
 // (a wavefront takes its points one after the other, so a small plan needs more workgroups more than
-// it needs fewer atomics).  The dI0 tile holds the patches of a full tile of windows wherever the
+// it needs fewer atomics; twice as many for the largest shape, whose wavefronts take sixteen: one 800x700
+// pair, stride 2, support 15, illumination model, 137,016 points, 325 us for 347, and where one ninth of
+// them converged in a corner 85 for 152).  The dI0 tile holds the patches of a full tile of windows wherever the
 // centroids fall in them; the dI1 tile leaves room for a quarter more spread and 8 px of it.
 void adjoint_tile_shape(AdjPair &P, int nx, int ny, int s, int win, int stride, int64_t n)
 {
@@ -157,7 +174,7 @@ void adjoint_tile_shape(AdjPair &P, int nx, int ny, int s, int win, int stride, 
     const int W0 = s + 3, W1 = s + 1;
     static const int shapes[][2] = {{16, 8}, {8, 8}, {8, 4}, {4, 4}};
     for (const auto &sh : shapes) {
-        if (n < kMinTiles * sh[0] * sh[1]) continue;
+        if (n < (sh[0] == 16 ? 2 : 1) * kMinTiles * sh[0] * sh[1]) continue;
         const int64_t ex = (int64_t)(sh[0] - 1) * stride, ey = (int64_t)(sh[1] - 1) * stride;
         const int64_t w0 = W0 + ex + win - 1, h0 = W0 + ey + win - 1;
         const int64_t w1 = W1 + ex + ex / 4 + win + 7, h1 = W1 + ey + ey / 4 + win + 7;

@@ -40,10 +40,10 @@ def _tile_shape(nx, ny, support, window, stride, n):
 
 @pytest.mark.parametrize("illum", [False, True])
 @pytest.mark.parametrize("support,window,stride,points,shape", [
-    (5, 3, 1, 32768, (8, 4)), (5, 9, 1, 131072, (16, 8)), (7, 9, 1, 65536, (8, 8)), (7, 3, 2, 131072, (16, 8)),
-    (9, 3, 1, 16384, (4, 4)), (9, 9, 2, 65536, (8, 8)), (9, 9, 3, 131072, (16, 8)), (11, 3, 2, 16384, (4, 4)),
-    (11, 9, 1, 131072, (16, 8)), (15, 9, 1, 16384, (4, 4)), (15, 9, 3, 32768, (8, 4)), (15, 9, 2, 131072, (16, 8)),
-    (21, 9, 3, 16384, (4, 4)), (21, 9, 2, 32768, (8, 4)), (21, 9, 4, 65536, (8, 8)), (21, 9, 2, 131072, (16, 8)),
+    (5, 3, 1, 32768, (8, 4)), (5, 9, 1, 262144, (16, 8)), (7, 9, 1, 65536, (8, 8)), (7, 3, 2, 262144, (16, 8)),
+    (9, 3, 1, 16384, (4, 4)), (9, 9, 2, 65536, (8, 8)), (9, 9, 3, 262144, (16, 8)), (11, 3, 2, 16384, (4, 4)),
+    (11, 9, 1, 262144, (16, 8)), (15, 9, 1, 16384, (4, 4)), (15, 9, 3, 32768, (8, 4)), (15, 9, 2, 262144, (16, 8)),
+    (21, 9, 3, 16384, (4, 4)), (21, 9, 2, 32768, (8, 4)), (21, 9, 4, 65536, (8, 8)), (21, 9, 2, 262144, (16, 8)),
 ])
 def test_tile_shape_against_oracle(support, window, stride, points, shape, illum):
     rng = np.random.default_rng(support + 100 * stride + window + 1000 * illum)
@@ -92,4 +92,39 @@ def test_tile_shape_against_oracle(support, window, stride, points, shape, illum
             print(f"\ns{support} w{window} stride {stride} {'IM ' if illum else ''}tiles {shape} converged {conv.sum()} "
                   f"of {len(P)} rel {rel:.1e}", flush=True)
             assert rel <= 1e-4
+    plan.close()
+
+
+@pytest.mark.parametrize("illum", [False, True])
+@pytest.mark.parametrize("support", [5, 9, 21])
+def test_few_points_of_a_tile(support, illum):
+    """One to a dozen converged points in a tile, around the number from which on the LDS tiles are used."""
+    rng = np.random.default_rng(support + illum)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    W, H, window, stride = 301, 259, 3, 1
+    I0 = np.rint(synth.smoothed_noise(rng, W, H, 1.0 if illum else 2.0))
+    I1 = I0 if illum else np.rint(np.clip(I0 + 0.5 * rng.normal(size=I0.shape), 0, 255))
+    P = oracle.detect(I0.astype(np.uint8), window, stride)[0].astype(np.float32)
+    nx, ny = W - window + 1, H - window + 1
+    tx, ty = _tile_shape(nx, ny, support, window, stride, nx * ny)
+    ky, kx = np.divmod(np.arange(nx * ny), nx)
+    tile = (ky // ty) * 1000 + kx // tx
+    share = (tile * 7 % 13) / (tx * ty)  # 0 to 12 points of every tile
+    st = np.where(rng.uniform(size=len(P)) < share, 0, 2).astype(np.uint8)
+    per_tile = np.unique(tile[st == 0], return_counts=True)[1]
+    assert per_tile.min() == 1 and per_tile.max() > 10 and all((per_tile == k).sum() > 3 for k in range(4, 9))
+    u = (0.0 if illum else 0.02) * rng.normal(size=P.shape).astype(np.float32)
+    df = rng.normal(size=P.shape).astype(np.float32)
+    plan = dgf.Batch([(dev(I0.astype(np.uint8)), dev(I1.astype(np.uint8)), window, stride)], 1, support, 1,
+                     opts=dgf.TrackOpts(illum=illum))
+    _, views = plan.backward(dev(df), points=dev(P), flow=dev(u), status=dev(st),
+                             illum=torch.zeros((len(P), 2), device="cuda") if illum else None)
+    torch.cuda.synchronize()
+    c, f64 = st == 0, lambda a: np.asarray(a, np.float64)
+    args = [f64(I0), f64(I1), f64(P)[c], support, f64(u)[c]]
+    ref = oracle.track_grad_illum(*args, f64(0 * u)[c], st[c], f64(df)[c]) if illum else oracle.track_grad(*args, st[c], f64(df)[c])
+    for g, o in zip(views[0], ref):
+        rel = np.linalg.norm(g.cpu().numpy() - o) / np.linalg.norm(o)
+        print(f"s{support} {'IM ' if illum else ''}tiles {(tx, ty)} converged {c.sum()} rel {rel:.1e}", flush=True)
+        assert rel <= 1e-4
     plan.close()
