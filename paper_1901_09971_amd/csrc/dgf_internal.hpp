@@ -380,10 +380,14 @@ __device__ __forceinline__ bool stage_u8_w64(float *lds, int lp, const uint8_t *
 
 // stage_rect's interior case for float images: eight lanes per row, four texels per lane by one
 // 16-byte load (rows need only be 4-byte aligned), B steps of LPP / 8 rows in flight.  Qualifies when
-// cols <= 32 and every group of four lies inside the image; returns false, staging nothing,
-// otherwise.  When the row's last group fits the LDS row pitch it writes all four words into the
-// padding, which no reader looks at.  (One texel per lane and two rows in flight made a 20-row tile ten
-// round trips to L2: the tracker took 109 us on a 640x480 float pair at support 15, 99 now.)
+// cols <= 32 and every group of four lies inside the image, for every point of the wavefront: with some
+// staged here and some by stage_rect the wavefront would wait for both in turn, which on coarse levels, where
+// many tiles cross the border, cost more than the wider loads gave (3,000 points of a 640x480 pair, three
+// levels, support 11, least squares: 49 us before this form, 64 so, 49 now).  Returns false, staging
+// nothing, otherwise.  When the row's last group fits the LDS row pitch it writes all four words into the
+// padding, which no reader looks at.  (One texel per lane and two rows in flight makes a 20-row tile ten
+// round trips to L2: 18,000 points of that pair at support 5 52 -> 45 us, at 11 59 -> 54, at 15 88 -> 84,
+// at 21 95 -> 88.)
 template <int LPP, int B>
 __device__ __forceinline__ bool stage_f32(float *lds, int lp, const uint8_t *base, int64_t pitch, int W, int H, int ox,
                                           int oy, int rows, int cols, int li)
@@ -391,7 +395,8 @@ __device__ __forceinline__ bool stage_f32(float *lds, int lp, const uint8_t *bas
     typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
     typedef const __attribute__((address_space(1))) uint8_t gbyte;
     const int n4 = (cols + 3) >> 2;
-    if (!(cols <= 32 && ox >= 0 && oy >= 0 && ox + 4 * n4 <= W && oy + rows <= H)) return false;
+    const bool inside = cols <= 32 && ox >= 0 && oy >= 0 && ox + 4 * n4 <= W && oy + rows <= H;
+    if (LPP == 64 ? !inside : __ballot(!inside) != 0ull) return false;
     constexpr int step = LPP / 8;
     const int r0 = li >> 3, c4 = (li & 7) << 2;
     if (c4 >= cols) return true;
@@ -436,7 +441,7 @@ __device__ __forceinline__ void stage_tile(float *lds, int lp, const uint8_t *ba
     if constexpr (LPP == 64 && sizeof(PixT) == 1)
         if (stage_u8_w64<NS, B, CROWS>(lds, lp, base, pitch, W, H, ox, oy, rows, cols, li)) return;
     if constexpr (sizeof(PixT) == 4)
-        if (stage_f32<LPP, LPP == 64 ? B : 5>(lds, lp, base, pitch, W, H, ox, oy, rows, cols, li)) return;
+        if (stage_f32<LPP, LPP == 64 ? B : 2>(lds, lp, base, pitch, W, H, ox, oy, rows, cols, li)) return;
     stage_rect<LPP, PixT>(lds, lp, base, pitch, W, H, ox, oy, rows, cols, stage_lanes<LPP>(cols, li));
 }
 
