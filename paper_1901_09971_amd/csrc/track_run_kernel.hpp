@@ -111,9 +111,13 @@ __device__ __forceinline__ bool group_any(bool p)
 // registers), with the illumination model five (96, seven spilled on uint8: support 21 at 1242x375
 // 378 -> 364 us); 32 lanes and ten pixels, support 15, plain uint8 five (214 -> 207), with the
 // model four (349 -> 329).  32 lanes, support 9 with the model lost by it (216 -> 229, four to
-// thirteen spilled), and 16 lanes are held to three or four waves by LDS.
-constexpr int run_min_waves(int lpp, int ppl, int bytes, bool im)
+// thirteen spilled), and 16 lanes are held to three or four waves by LDS.  With cross supports only the plain
+// 64-lane form gains (uint8, support 15, 3,000 points of a 640x480 pair 97 -> 109 when held, support 21
+// with the model 66 -> 71).  Few points leave the waves without work: at 3,000 points the held shapes take
+// 1.00 to 1.04 of the time, at 18,000 0.94 to 0.98.
+constexpr int run_min_waves(int lpp, int ppl, int bytes, bool im, bool cross)
 {
+    if (cross) return lpp == 64 && !im ? 6 : 1;
     if (lpp == 64) return im ? 5 : 6;
     if (lpp == 32 && ppl == 10) return im ? 4 : bytes == 1 ? 5 : 1;
     return 1;
@@ -124,7 +128,7 @@ constexpr int run_min_waves(int lpp, int ppl, int bytes, bool im)
 // compile-time, so a single-pair square-window launch carries no batch bookkeeping, no per-pixel
 // support mask and no branch on the robust norm.
 template <int LPP, int SEG, int R, int TP, int S, typename PixT, bool IM, int MODE, bool CROSS, bool BATCH>
-__global__ __launch_bounds__(256, run_min_waves(LPP, SEG * R, sizeof(PixT), IM)) void k_track_run(TrackParams P)
+__global__ __launch_bounds__(256, run_min_waves(LPP, SEG * R, sizeof(PixT), IM, CROSS)) void k_track_run(TrackParams P)
 {
     constexpr int PPW = 64 / LPP;
     constexpr int PPL = SEG * R;
