@@ -46,7 +46,7 @@ constexpr int kRelaxThreads = 64 * kRWaves;
 constexpr int kInner = 4;            // relaxation iterations of a round, between two checks for changes
 constexpr int kExchange = 8;         // rounds between two halo exchanges
 constexpr int kMaxRounds = 2048;     // rounds per tile and launch
-constexpr int kMaxPolls = 4096;      // halo polls of a still tile per launch
+constexpr int kMaxPolls = 1 << 16;     // halo polls of a still tile per launch
 constexpr int kPollSleep = 2;        // 64-cycle units between two polls
 constexpr int kLinger = 32;          // halo polls of a still tile per launch of a grid that does not fit the chip
 constexpr int kStartPolls = 256;     // polls a resident grid waits for tiles that have not started
@@ -212,11 +212,12 @@ __device__ __forceinline__ uint64_t key_relax(uint64_t mine, uint64_t from, uint
         asm("v_min_f64 %0, %0, %1" : "+v"(a) : "v"(v));
         return __builtin_bit_cast(uint64_t, a);
     } else {
-        // a sum at or beyond all ones is no distance (the wavefront's end lanes shift in zeros, whose sum with
-        // a wall is all ones exactly)
+        // an overflowing sum is no key.  (Zero plus a wall does not overflow: the end lanes, into which the
+        // shifts bring zeros, may take it, but nothing comes of it: no step leads out of all ones.)
         const uint32_t d = hi + c;
-        const uint64_t v = ((uint64_t)d << 32) | lo;
-        return d >= hi && d != 0xFFFFFFFFu && v < mine ? v : mine;
+        const bool over = d < hi;
+        const uint64_t v = ((uint64_t)(over ? 0xFFFFFFFFu : d) << 32) | (over ? 0xFFFFFFFFu : lo);
+        return v < mine ? v : mine;
     }
 }
 
