@@ -46,7 +46,7 @@ constexpr int kRelaxThreads = 64 * kRWaves;
 constexpr int kInner = 4;            // relaxation iterations of a round, between two checks for changes
 constexpr int kExchange = 8;         // rounds between two halo exchanges
 constexpr int kMaxRounds = 2048;     // rounds per tile and launch
-constexpr int kMaxPolls = 1 << 16;     // halo polls of a still tile per launch
+constexpr int kMaxPolls = 4096;      // halo polls of a still tile per launch
 constexpr int kPollSleep = 2;        // 64-cycle units between two polls
 constexpr int kLinger = 32;          // halo polls of a still tile per launch of a grid that does not fit the chip
 constexpr int kStartPolls = 256;     // polls a resident grid waits for tiles that have not started
