@@ -1,7 +1,8 @@
 """The dense interpolation at the limits of its parameters and surroundings: no seed at all with both key
 forms of the relaxation (distances beyond the fast form's range come with a large kappa on a large
 frame); calls side by side on several streams, whose grids are not resident at once; a frame of more
-tiles than the chip holds whose distances cross all its rows of tiles; half-distances and step costs
+tiles than the chip holds whose distances cross all its rows of tiles; long paths through a resident
+grid, whose tiles wait for them; half-distances and step costs
 far from the defaults, whose neighbour searches take no longer than the defaults'."""
 import numpy as np
 import pytest
@@ -111,3 +112,17 @@ def test_large_half_distance_takes_no_longer():
     base, far = ms(64), ms(1 << 20)
     print(f"half-distance 2^20 takes {far / base:.2f} of 64", flush=True)
     assert far < 1.7 * base
+
+
+@pytest.mark.parametrize("W,H,kappa", [(2048, 1024, 8), (1242, 375, 1 << 20), (8000, 4, 8), (4, 8000, 8)])
+def test_long_paths_settle_in_one_launch(W, H, kappa):
+    """One seed in a corner of a frame that fits the chip: the far tiles wait for the front through the
+    whole of the first launch, and the second finds nothing to change."""
+    rng = np.random.default_rng(W)
+    I0 = torch.from_numpy(rng.integers(0, 256, (H, W)).astype(np.uint8)).cuda()
+    P = torch.tensor([[W - 2.0, H - 2.0]], device="cuda")
+    F, st, opts = torch.ones_like(P), torch.zeros(1, dtype=torch.uint8, device="cuda"), dgf.EpicOpts(kappa=kappa)
+    _, want = dgf.epic(I0, P, F, st, opts=opts, return_aux=True)
+    _, status, aux = dgf.epic_async(I0, P, F, st, opts=opts, max_relax=2, return_aux=True)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0 and torch.equal(aux["dist"], want["dist"])
