@@ -534,15 +534,26 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
 
 // Seed graph: every right / down pixel pair whose cells differ gives both cells an edge of
 // length D(p) + step(p, q) + D(q); each row keeps the least length per neighbour.  A workgroup takes a
-// tile of 64 x 32 pixels and keeps the least length of each pair of cells it meets in a hash table in
-// LDS; only the table's entries then go to the rows in device memory, whose atomics are what the
-// launch waits for: a pair of cells meets along several pixels, and the rows took one insertion for
-// each run of them (2048x1024, 117,238 seeds: 427 -> 74 us with k_epic_least; 1242x375: 82 -> 26).
-// An entry that finds no place in the table within kGraphProbes steps goes to the rows directly.
-constexpr int kGraphW = 64, kGraphRows = 8, kGraphWaves = 4; // tile: 64 columns, 8 rows per wavefront
-constexpr int kGraphHash = 1024;
-constexpr int kGraphProbes = 32;
+// tile of 64 columns and four wavefronts of ROWS rows and keeps the least length of each pair of cells it
+// meets in a hash table in LDS; only the table's entries then go to the rows in device memory, whose
+// atomics are what the launch waits for: a pair of cells meets along several pixels, and the rows took
+// one insertion for each run of them.  An entry that finds no place in the table within kGraphProbes
+// steps, or finds the table full but for an eighth, goes to the rows directly.
+//
+// A lane's pixels and insertions are a serial chain, so a frame that leaves CUs without a workgroup
+// takes fewer rows: eight from 2^19 pixels on (2048x1024, a seed every 5 px: 53 us, 90 with two; the
+// one insertion for each run 426), two below (640x480, every 2 px: 39 us, 107 with eight; 86), one below
+// 2^16 (128x96, a seed on every pixel: 12 us, 23 with two, 133 with eight; 12).  A table of 1,024
+// entries took 32 steps for each of the 1,500 pairs that meet in 64 x 32 pixels with a seed every 2 px
+// (1242x375: 109 us, 51 now).
+constexpr int kGraphW = 64, kGraphWaves = 4;
+constexpr int kGraphHash = 2048;
+constexpr int kGraphProbes = 8;
+constexpr int kGraphFull = kGraphHash / 8 * 7;
 
+int graph_rows(int64_t pixels) { return pixels >= 1 << 19 ? 8 : pixels >= 1 << 16 ? 2 : 1; }
+
+template <int ROWS>
 __global__ __launch_bounds__(64 * kGraphWaves) void k_epic_graph(int W, int H, int kappa, const uint64_t *keys,
                                                                  const uint16_t *E, EpicWs ws, uint32_t *err,
                                                                  const uint32_t *unsettled)
@@ -559,7 +570,7 @@ __global__ __launch_bounds__(64 * kGraphWaves) void k_epic_graph(int W, int H, i
     if (threadIdx.x == 0) used = 0;
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int x = (int)blockIdx.x * kGraphW + lane, y0 = ((int)blockIdx.y * kGraphWaves + wave) * kGraphRows;
+    const int x = (int)blockIdx.x * kGraphW + lane, y0 = ((int)blockIdx.y * kGraphWaves + wave) * ROWS;
     auto length = [&](uint64_t kp, uint32_t ep, uint64_t kq, uint32_t eq) {
         const uint64_t w64 = (kp >> 32) + (uint64_t)kappa + ep + eq + (kq >> 32);
         return w64 < 0xFFFFFFFFull ? (uint32_t)w64 : 0xFFFFFFFFu;
@@ -571,6 +582,7 @@ __global__ __launch_bounds__(64 * kGraphWaves) void k_epic_graph(int W, int H, i
         const unsigned long long pair = ((unsigned long long)min(ls, lt) << 32) | max(ls, lt);
         uint32_t h = (ls ^ lt) * 2654435761u + (ls + lt) * 2246822519u;
         h = (h >> 16) & (kGraphHash - 1);
+        if (__hip_atomic_load(&used, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= kGraphFull) return true;
         for (int probe = 0; probe < kGraphProbes; ++probe) {
             const unsigned long long cur = atomicCAS(&hkey[h], (unsigned long long)kNoKey, pair);
             if (cur == kNoKey) list[atomicAdd(&used, 1)] = (uint16_t)h;
@@ -586,20 +598,20 @@ __global__ __launch_bounds__(64 * kGraphWaves) void k_epic_graph(int W, int H, i
     auto edge_at = [&](int xx, int yy) { return (uint32_t)E[(int64_t)yy * W + xx]; };
     if (x < W) {
         // all the keys first: the rows' and the column to the right of the tile
-        uint64_t k[kGraphRows + 1], kr[kGraphRows];
-        uint32_t e[kGraphRows + 1], er[kGraphRows], missed = 0u;
+        uint64_t k[ROWS + 1], kr[ROWS];
+        uint32_t e[ROWS + 1], er[ROWS], missed = 0u;
 #pragma unroll
-        for (int j = 0; j <= kGraphRows; ++j) {
+        for (int j = 0; j <= ROWS; ++j) {
             const int y = min(y0 + j, H - 1);
             k[j] = key_at(x, y);
             e[j] = edge_at(x, y);
-            if (j < kGraphRows) {
+            if (j < ROWS) {
                 kr[j] = key_at(min(x + 1, W - 1), y);
                 er[j] = edge_at(min(x + 1, W - 1), y);
             }
         }
 #pragma unroll
-        for (int j = 0; j < kGraphRows; ++j) {
+        for (int j = 0; j < ROWS; ++j) {
             if (y0 + j >= H) break;
             if (x + 1 < W && meet(k[j], e[j], kr[j], er[j])) missed |= 1u << (2 * j);
             if (y0 + j + 1 < H && meet(k[j], e[j], k[j + 1], e[j + 1])) missed |= 2u << (2 * j);
@@ -1112,8 +1124,9 @@ int epic_run(const dgf_image *I0, const float *points, const float *flow, const 
     // everything after the partition; unsettled (nullable): nothing is done when this word is not zero
     auto finish = [&](const uint32_t *unsettled) {
         if (n > 0) {
-            const int gh = kGraphWaves * kGraphRows;
-            hipLaunchKernelGGL(k_epic_graph, dim3((unsigned)((W + kGraphW - 1) / kGraphW), (unsigned)((H + gh - 1) / gh)),
+            const int rows = graph_rows(N), gh = kGraphWaves * rows;
+            const auto graph = rows == 8 ? k_epic_graph<8> : rows == 2 ? k_epic_graph<2> : k_epic_graph<1>;
+            hipLaunchKernelGGL(graph, dim3((unsigned)((W + kGraphW - 1) / kGraphW), (unsigned)((H + gh - 1) / gh)),
                                dim3(64 * kGraphWaves), 0, st, W, H, o.kappa, (const uint64_t *)ws.keys,
                                (const uint16_t *)ws.E, ws, err, unsettled);
             if (hipGetLastError() != hipSuccess) return false;

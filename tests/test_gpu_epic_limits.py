@@ -3,11 +3,13 @@ forms of the relaxation (distances beyond the fast form's range come with a larg
 frame); calls side by side on several streams, whose grids are not resident at once; a frame of more
 tiles than the chip holds whose distances cross all its rows of tiles; long paths through a resident
 grid, whose tiles wait for them; half-distances and step costs
-far from the defaults, whose neighbour searches take no longer than the defaults'."""
+far from the defaults, whose neighbour searches take no longer than the defaults'; seeds denser than the seed
+graph's tables hold, at every height of its tiles."""
 import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_1901_09971_amd as dgf
 from paper_1901_09971_amd import synth
 from test_gpu_epic import _run_both
@@ -126,3 +128,26 @@ def test_long_paths_settle_in_one_launch(W, H, kappa):
     _, status, aux = dgf.epic_async(I0, P, F, st, opts=opts, max_relax=2, return_aux=True)
     torch.cuda.synchronize()
     assert int(status.item()) == 0 and torch.equal(aux["dist"], want["dist"])
+
+
+@pytest.mark.parametrize("W,H,step", [(255, 256, 6), (256, 256, 6), (301, 227, 2), (760, 700, 7), (1025, 513, 7)])
+def test_graph_tiles(W, H, step):
+    """Frames around the sizes at which the graph's tiles change height; a seed on every pixel of two
+    rectangles, so that the tables of the tiles there run over, and every few pixels elsewhere."""
+    rng = np.random.default_rng(W + step)
+    I0 = rng.integers(0, 256, (H, W)).astype(np.uint8)
+    on = np.zeros((H, W), bool)
+    on[::step, ::step] = True
+    on[40:110, 60:190] = True
+    on[H - 20:, W - 70:] = True
+    y, x = np.nonzero(on)
+    P = np.stack([x, y], 1).astype(np.float32)
+    F, st = rng.normal(size=P.shape).astype(np.float32), np.zeros(len(P), np.uint8)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    _, aux = dgf.epic(t(I0), t(P), t(F), t(st), opts=dgf.EpicOpts(k=8), return_aux=True)
+    torch.cuda.synchronize()
+    g = {k: v.cpu().numpy() for k, v in aux.items()}
+    _, o = oracle.epic(I0, P.astype(np.float64), F.astype(np.float64), st, k=8, full=True)
+    assert np.array_equal(g["labels"], o["L"])
+    assert np.array_equal(g["nbr"], o["nb"])
+    assert np.array_equal(g["nbr_dist"].view(np.uint32).astype(np.int64), np.where(o["nd"] < 0, 0xFFFFFFFF, o["nd"]))
