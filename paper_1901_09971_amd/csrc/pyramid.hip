@@ -231,10 +231,9 @@ constexpr size_t kFrontDetectLds = 2 * (size_t)PC_N0P * PC_N0;
 // ---- float chains: the same tiles, a float per byte.  Sums of whole products, 4 (a + b) exact and
 // 6 c fused into its sum, then the scale; four outputs per step from 16-byte LDS reads.  Four levels of a
 // 640x480 pair take 8.9 us, a float per step 12.5, a launch per level 31 and the gaps between them.
-template <int M>
+template <int M, int T>
 constexpr size_t chain_f32_floats(int part) // two level buffers in turn (+ the float4 read past the last row), horizontal sums
 {
-    constexpr int T = chain_tile(M);
     const size_t n0 = (size_t)pc_width(M, T) * pc_pitch(M, T) + 4, n1 = (size_t)pc_width(M - 1, T) * pc_pitch(M - 1, T) + 4;
     const size_t h = (size_t)pc_width(M, T) * pc_pitch(M - 1, T);
     return part == 0 ? n0 : part == 1 ? n0 + n1 : n0 + n1 + h;
@@ -290,12 +289,13 @@ __device__ __forceinline__ void chain_level_f32(const PyrChain &A, int f, int bx
     if constexpr (J > 1) chain_replicate<HO, PO>(out, ux, uy, W, H);
 }
 
-template <int M>
+template <int M, int T>
 __global__ __launch_bounds__(kChainThreads) void k_pyr_chain_f32(PyrChain A)
 {
     extern __shared__ __align__(16) float chain_lds[];
-    float *const b0 = chain_lds, *const b1 = chain_lds + chain_f32_floats<M>(0), *const hs = chain_lds + chain_f32_floats<M>(1);
-    constexpr int T = chain_tile(M), kHalo = (2 << M) - 2, kOwn = T << M;
+    float *const b0 = chain_lds, *const b1 = chain_lds + chain_f32_floats<M, T>(0),
+                *const hs = chain_lds + chain_f32_floats<M, T>(1);
+    constexpr int kHalo = (2 << M) - 2, kOwn = T << M;
     const int bx = (int)blockIdx.x, by = (int)blockIdx.y, f = (int)blockIdx.z;
     {
         // (rows of any alignment: a float per lane, the columns past the range left out)
@@ -324,20 +324,34 @@ __global__ __launch_bounds__(kChainThreads) void k_pyr_chain_f32(PyrChain A)
     if constexpr (M > 3) chain_level_f32<M - 3, T>(A, f, bx, by, b1, b0, hs);
 }
 
+// A large float frame's first level goes by itself: a block of more levels re-reads up to 2.9 times its
+// pixels, which costs more than a launch from about a million pixels on (five levels of a 2048x1024
+// pair: 15 us, 30 in one launch; of a 1242x375 pair 9 in one, 12 in two).  Its tiles are 32 pixels wide: with
+// 16 a block stages 35 x 35 floats for 256 outputs and most of its lanes idle (2048x1024 pair, that
+// level alone: 11.3 us, 6.4 now, 9.4 in tiles of 64 x 16 by 256 lanes; 4096x2160 35, 24, 35).
+static bool chain_f32_alone(int W, int H) { return (int64_t)W * H > (1 << 20); }
+
 static hipError_t launch_pyr_chain_f32(const PyrChain &A, int njobs, hipStream_t st)
 {
     if (A.m < 1 || A.m > PC_MAXM || njobs < 1 || njobs > 2) return hipErrorInvalidValue;
-    const int T = chain_tile(A.m);
-    const dim3 grid((A.W[A.m] + T - 1) / T, (A.H[A.m] + T - 1) / T, njobs);
-    auto go = [&](auto m) {
-        hipLaunchKernelGGL(k_pyr_chain_f32<m.value>, grid, dim3(kChainThreads), sizeof(float) * chain_f32_floats<m.value>(2), st, A);
+    auto go = [&](auto m, auto tile) {
+        constexpr int M = m.value, T = tile.value;
+        const dim3 grid((A.W[M] + T - 1) / T, (A.H[M] + T - 1) / T, njobs);
+        constexpr size_t lds = sizeof(float) * chain_f32_floats<M, T>(2);
+        hipLaunchKernelGGL((k_pyr_chain_f32<M, T>), grid, dim3(kChainThreads), lds, st, A);
     };
+    using std::integral_constant;
     static_assert(PC_MAXM == 4, "cases");
     switch (A.m) {
-    case 1: go(std::integral_constant<int, 1>()); break;
-    case 2: go(std::integral_constant<int, 2>()); break;
-    case 3: go(std::integral_constant<int, 3>()); break;
-    default: go(std::integral_constant<int, 4>()); break;
+    case 1:
+        if (chain_f32_alone(A.W[0], A.H[0]))
+            go(integral_constant<int, 1>(), integral_constant<int, 32>());
+        else
+            go(integral_constant<int, 1>(), integral_constant<int, chain_tile(1)>());
+        break;
+    case 2: go(integral_constant<int, 2>(), integral_constant<int, chain_tile(2)>()); break;
+    case 3: go(integral_constant<int, 3>(), integral_constant<int, chain_tile(3)>()); break;
+    default: go(integral_constant<int, 4>(), integral_constant<int, chain_tile(4)>()); break;
     }
     return hipGetLastError();
 }
@@ -374,10 +388,7 @@ hipError_t launch_pyr_chains(const uint8_t *const srcs[2], const int64_t src_pit
     }
     for (int s = 0, m; s + 1 < levels; s += m) {
         PyrChain A{};
-        // a large float frame's first level goes by itself: a block of more levels re-reads up to 2.9
-        // times its pixels, which costs more than a launch from about a million pixels on (five levels of a
-        // 2048x1024 pair: 17 us, 30 in one launch; of a 1242x375 pair 9 in one, 12 in two)
-        const bool alone = dtype != DGF_U8 && (int64_t)Wl[s] * Hl[s] > (1 << 20);
+        const bool alone = dtype != DGF_U8 && chain_f32_alone(Wl[s], Hl[s]);
         m = alone ? 1 : levels - 1 - s < PC_MAXM ? levels - 1 - s : PC_MAXM;
         A.m = m;
         for (int f = 0; f < njobs; ++f) {
