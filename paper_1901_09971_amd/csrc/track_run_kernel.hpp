@@ -108,27 +108,32 @@ __device__ __forceinline__ bool group_any(bool p)
 
 // Waves per SIMD that a shape's registers are held to.  The kernel is issue bound (VALU about nine
 // tenths busy), and one more wave pays where it costs few or no spills: 64 lanes, plain, six (80
-// registers), with the illumination model five (96, seven spilled on uint8: support 21 at 1242x375
-// 378 -> 364 us); 32 lanes and ten pixels, support 15, plain uint8 five (214 -> 207), with the
-// model four (349 -> 329).  32 lanes, support 9 with the model lost by it (216 -> 229, four to
-// thirteen spilled), and 16 lanes are held to three or four waves by LDS.  With cross supports only the plain
-// 64-lane form gains (uint8, support 15, 3,000 points of a 640x480 pair 97 -> 109 when held, support 21
-// with the model 66 -> 71).  Few points leave the waves without work: at 3,000 points the held shapes take
-// 1.00 to 1.04 of the time, at 18,000 0.94 to 0.98.
-constexpr int run_min_waves(int lpp, int ppl, int bytes, bool im, bool cross)
+// registers), and in launches of many wavefronts (HELD) with the illumination model five (96, seven spilled
+// on uint8: support 21 at 1242x375 378 -> 364 us); 32 lanes and ten pixels, support 15, plain uint8 five
+// (214 -> 207), with the model four (349 -> 329).  32 lanes, support 9 with the model lost by it
+// (216 -> 229, four to thirteen spilled), and 16 lanes are held to three or four waves by LDS.  With cross
+// supports only the plain 64-lane form gains (uint8, support 15, 3,000 points of a 640x480 pair 97 -> 109
+// when held, support 21 with the model 66 -> 71).
+constexpr int run_min_waves(int lpp, int ppl, int bytes, bool im, bool cross, bool held)
 {
-    if (cross) return lpp == 64 && !im ? 6 : 1;
-    if (lpp == 64) return im ? 5 : 6;
+    if (lpp == 64 && !im) return 6;
+    if (cross || !held) return 1;
+    if (lpp == 64) return 5;
     if (lpp == 32 && ppl == 10) return im ? 4 : bytes == 1 ? 5 : 1;
     return 1;
 }
+
+// Whether a launch of this many wavefronts takes the held form: from two rounds of what the chip then
+// holds (1,024 SIMDs).  Below, the last round's end decides, and the spills cost (uint8 1242x375, support
+// 21 with the model, 6,000 points: 154 us, 174 held; support 15, 4,000 points: 106, 110 held).
+constexpr bool run_held(int64_t waves, int min_waves) { return waves >= 2 * 1024 * (int64_t)min_waves; }
 
 // MODE (ROBUST_L2 / HAMPEL / HARD), CROSS (adaptive
 // cross-based supports) and BATCH (a batch plan's persistent launch rather than one pair) are
 // compile-time, so a single-pair square-window launch carries no batch bookkeeping, no per-pixel
 // support mask and no branch on the robust norm.
-template <int LPP, int SEG, int R, int TP, int S, typename PixT, bool IM, int MODE, bool CROSS, bool BATCH>
-__global__ __launch_bounds__(256, run_min_waves(LPP, SEG * R, sizeof(PixT), IM, CROSS)) void k_track_run(TrackParams P)
+template <int LPP, int SEG, int R, int TP, int S, typename PixT, bool IM, int MODE, bool CROSS, bool BATCH, bool HELD>
+__global__ __launch_bounds__(256, run_min_waves(LPP, SEG * R, sizeof(PixT), IM, CROSS, HELD)) void k_track_run(TrackParams P)
 {
     constexpr int PPW = 64 / LPP;
     constexpr int PPL = SEG * R;
@@ -684,13 +689,27 @@ hipError_t launch_track_run_t(const TrackParams &P, int wpb, hipStream_t st)
     const int64_t blocks = P.npairs ? (waves + wpb - 1) / wpb : plain_blocks((waves + wpb - 1) / wpb, wpb, PPW);
     const size_t lds = (size_t)wpb * PPW * P.tile_floats * sizeof(float);
     const dim3 grid((unsigned)blocks), block(64 * wpb);
-    if (P.mode == ROBUST_L2)
-        hipLaunchKernelGGL((k_track_run<LPP, SEG, R, TP, S, PixT, IM, ROBUST_L2, CROSS, BATCH>), grid, block, lds, st, P);
-    else if (P.mode == ROBUST_HAMPEL)
-        hipLaunchKernelGGL((k_track_run<LPP, SEG, R, TP, S, PixT, IM, ROBUST_HAMPEL, CROSS, BATCH>), grid, block, lds, st,
-                           P);
-    else
-        hipLaunchKernelGGL((k_track_run<LPP, SEG, R, TP, S, PixT, IM, ROBUST_HARD, CROSS, BATCH>), grid, block, lds, st, P);
+    auto go = [&](auto held) {
+        if (P.mode == ROBUST_L2)
+            hipLaunchKernelGGL((k_track_run<LPP, SEG, R, TP, S, PixT, IM, ROBUST_L2, CROSS, BATCH, held.value>), grid, block,
+                               lds, st, P);
+        else if (P.mode == ROBUST_HAMPEL)
+            hipLaunchKernelGGL((k_track_run<LPP, SEG, R, TP, S, PixT, IM, ROBUST_HAMPEL, CROSS, BATCH, held.value>), grid,
+                               block, lds, st, P);
+        else
+            hipLaunchKernelGGL((k_track_run<LPP, SEG, R, TP, S, PixT, IM, ROBUST_HARD, CROSS, BATCH, held.value>), grid, block,
+                               lds, st, P);
+    };
+    // (a batch plan's persistent launch fills the chip)
+    constexpr int most = run_min_waves(LPP, SEG * R, sizeof(PixT), IM, CROSS, true);
+    if constexpr (!BATCH && most != run_min_waves(LPP, SEG * R, sizeof(PixT), IM, CROSS, false)) {
+        if (run_held(waves, most))
+            go(std::true_type());
+        else
+            go(std::false_type());
+    } else {
+        go(std::integral_constant<bool, BATCH>());
+    }
     return hipGetLastError();
 }
 
