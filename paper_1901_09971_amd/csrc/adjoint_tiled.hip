@@ -12,14 +12,14 @@ namespace dgf {
 // and go to the gradient maps once per workgroup.  The dI0 tile starts at the least patch origin
 // of the workgroup's converged points; the dI1 tile is centred on the median patch origin (the
 // points' flows differ); a patch that leaves its tile goes to device memory directly.  With one
-// wavefront and about 1,060 device atomics per point the atomics bound the launch (one 2048x1024
-// pair, stride 2, support 21, 262,382 converged points: 1.68 ms against 0.64 ms here, of which
-// 0.40 ms is VALU issue, 940 instructions per point); 16 x 8 points per workgroup leave about 110.
+// wavefront and about 1,060 device atomics per point the atomics bound the launch (four 2048x1024
+// pairs, stride 2, support 21, 701,685 converged points: 4.97 ms against 1.55 here, of which 1.17 ms
+// is VALU issue, 1,020 instructions per point); 16 x 8 points per workgroup leave about 110.
 // Eight wavefronts and at most 78 KB keep two workgroups on a CU, so one's ends overlap the other.
 // Where few of a tile's points converged, clearing and emptying its LDS tiles costs more than their
 // atomics: up to kAdjFew go to the maps directly (four 1242x375 pairs, stride 5, support 21, 73,112
-// points of which 2 % converged: 35 us, 48 through the tiles, 36 with a wavefront per point; 20 %:
-// 90, 86 and 130).  A wavefront takes up to eight points one after the other, so a small block of
+// points of which 2 % converged: 36 us, 48 through the tiles, 36 with a wavefront per point; 20 %:
+// 85, 87 and 130).  A wavefront takes up to eight points one after the other, so a small block of
 // converged points in a plan of others is the one pattern that a wavefront per point does faster (two
 // 520x400 pairs, stride 2, support 9, one ninth of the points in a corner: 36 us against 45).
 constexpr int kAdjWaves = 8;

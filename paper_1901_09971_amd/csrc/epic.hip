@@ -12,7 +12,7 @@
 //   k_epic_relax    62x32 tiles relaxed in registers (Bellman-Ford sweeps), exchanging border
 //                   pixels with their neighbours during the launch; a grid that fits the chip
 //                   settles in one launch, a larger one is launched until nothing changes
-//   k_epic_graph    adjacent-cell pairs, gathered per 64x32 tile in LDS, inserted into fixed-size
+//   k_epic_graph    adjacent-cell pairs, gathered per tile in LDS, inserted into fixed-size
 //                   per-seed adjacency rows
 //   k_epic_least    each seed's least edge
 //   k_epic_knn_fit  one wavefront per seed: Dijkstra on the seed graph with the frontier and a
@@ -253,8 +253,8 @@ __device__ __forceinline__ uint64_t key_shift(uint64_t k)
 // belong to a real path, so a launch in which no tile changes anything is at the fixed point.
 // What bounds it is the longest least path: its iterations (about 110 VALU instructions, 0.2 us with a
 // wavefront per SIMD) and its tile crossings (an exchange, about 2 us).  1242x375: 228 -> 128 us for the
-// launch that works and the one that confirms; 2048x1024 (1,088 tiles): 624 -> 324 us of relaxation
-// over 32 launches, 160 of them in the working one.  The form before kept 32x64 tiles in LDS, four pixels a lane, at about 28
+// launch that works and the one that confirms; 2048x1024 (1,088 tiles) 160 us in the working launch with
+// 117,238 seeds all over the frame, 257 and 441 with as many and more that leave stretches empty.  The form before kept 32x64 tiles in LDS, four pixels a lane, at about 28
 // instructions and 5 LDS accesses a pixel and iteration, one column or row per iteration.
 // Without `wait` a still tile looks for mail kLinger times before it leaves, so that a front that comes
 // down or up the rows of tiles on the chip together crosses more than one of them a launch: seeds along the
@@ -1185,9 +1185,8 @@ int epic_run(const dgf_image *I0, const float *points, const float *flow, const 
         const int limit = sync ? kMaxRelaxLaunches : max_relax;
         // a grid that fits the chip settles in its first launch and the second says so; where other work
         // keeps it from being resident for a while, any later launch may be the one that settles it, so all
-        // of them wait.  (With 128 workgroups that do not wait from the third launch on, one returns in 2.5 us
-        // instead of 5 on 1,088 tiles, but 4 calls side by side on 1400x700 frames of one seed could end unsettled
-        // after 32 launches.)
+        // of them wait.  (128 workgroups that do not wait, from the third launch on, saved 7 of 1,224 us on a
+        // 2048x1024 call, but 9 of 32 calls on four streams, 1600x900 frames of one seed, ended unsettled.)
         int done = 0; // launches so far; launch j uses counter set j mod kChunk
         auto relax = [&](int launches) {
             for (const int end = done + std::min(launches, limit - done); done < end; ++done) {
