@@ -487,7 +487,10 @@ __global__ __launch_bounds__(kRelaxThreads, 5) void k_epic_relax(int W, int H, i
         if ((ever >> j) & 1u) store_key(keys + at(y0 + j), own[j]);
     const bool wrote = __syncthreads_or(ever != 0u) != 0;
     if (threadIdx.x == 0) {
-        if (!settled) atomicAdd(now.open, 1u);
+        if (!settled) {
+            atomicAdd(now.open, 1u);
+            if (wait) store_word(now.done, kLeave); // (out of rounds or polls: nobody waits for this tile)
+        }
         if (wrote) atomicAdd(now.changed, 1u);
     }
 }
